@@ -308,8 +308,8 @@ fo_status fo_options_init(fo_options* o);
  * also counts the words fo_run_overlapped needs); NULL = no signalling.
  * counters[0, P) are the group counters: zeroed by the caller before the
  * launch and before any consumer of this run starts (see fo_reset_counters).
- * When a tile's stores are complete and visible to every chiplet, one
- * agent-scope increment is made on counters[group of its slot]; when the
+ * When a tile's stores are complete and visible to every chiplet, it is
+ * counted by an agent-scope add on counters[group of its slot]; when the
  * GEMM is done, counters[j] == target_j for every j < P.
  * counters[P, P + FO_DISPENSER_WORDS) hand out tile positions to the GEMM's
  * workgroups: they must be zero before the first launch on the array, and
@@ -322,6 +322,13 @@ fo_status fo_options_init(fo_options* o);
  * order and a workgroup that is not yet scheduled (its compute unit busy
  * with other work) holds no tile back; without counters, workgroup b
  * computes positions b, b + grid, b + 2*grid, ...
+ * Plans with 64x64 tiles: a workgroup computes a block of 128x128, 64x64 or
+ * (without counters) 64x32 or 32x32 outputs, chosen by the number of tiles
+ * against W; up to 2 W workgroups run at a time when no compute units are
+ * reserved, blocks take the plan's dispatch order with bands of the same
+ * height, and a block's tiles of one group are counted by one add. With a
+ * block per workgroup the position words stay untouched. Results do not depend
+ * on the block.
  * dev_plan: the plan's device image (fo_plan_to_device).
  * Errors: FO_ERR_ARG, FO_ERR_SHAPE (K % 64), FO_ERR_UNSUPPORTED (tile shape
  * other than 256x128 / 256x256 / 64x64), FO_ERR_HIP (launch failure).

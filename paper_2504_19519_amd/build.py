@@ -19,7 +19,7 @@ CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libfo.so")
 USAGE = os.path.join(OBJ, "resource_usage.json")
-SOURCES = ["plan.cpp", "gemm.hip", "consume.hip", "post.hip", "runtime.hip"]
+SOURCES = ["plan.cpp", "gemm.hip", "gemm_block.hip", "consume.hip", "post.hip", "runtime.hip"]
 ARCH = "gfx950"
 
 

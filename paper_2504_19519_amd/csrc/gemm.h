@@ -13,6 +13,8 @@ struct GemmArgs {
     int64_t M, N, K;
     int32_t tiles_m, tiles_n;
     int32_t order, group_m, num_xcds;
+    int32_t blocks_m, blocks_n;    // block grid and band height of the 64x64 plans' kernels (gemm_block.hip)
+    int32_t block_band;
     int32_t pattern, num_dest;
     const int32_t* tile_to_slot;   // device plan tables (may be null for ROWMAJOR)
     const int32_t* slot_group;
@@ -33,6 +35,8 @@ struct GemmArgs {
 // grid: number of persistent workgroups (at most the number of tiles; with
 // a dispenser, a multiple of num_dispensers).
 hipError_t launch_gemm(int dtype, int tile_m, int tile_n, const GemmArgs& a, int grid, hipStream_t s);
+// Plans with 64x64 tiles (gemm_block.hip); wave_width: the plan's W.
+hipError_t launch_gemm64(int dtype, GemmArgs a, int wave_width, bool share_cus, hipStream_t s);
 bool gemm_tile_supported(int tile_m, int tile_n);
 
 }  // namespace fo

@@ -8,25 +8,22 @@
 // slot in the reordered output (Section 3.3 Approach (1)).
 //
 // Main loop, k steps of 64, A and W tiles moving from memory straight into an
-// LDS ring of STAGES stages (direct global-to-LDS loads, XOR-swizzled rows for
+// LDS ring of two stages (direct global-to-LDS loads, XOR-swizzled rows for
 // conflict-free 16-byte fragment reads); fragments of the next MFMA k step are
 // read while the MFMAs of the current one run, and every LDS read and load
-// issue sits in the shadow of an MFMA. Two forms:
-//   256x256 and 256x128 tiles: 4 waves of 128 x 128 (128 x 64), one per
-//     SIMD, v_mfma_f32_16x16x32 in inline asm with the accumulators tied in
-//     place, two stages; a wave of 128 x 128 reads 2/3 of the LDS bytes per
-//     flop that 8 waves of 128 x 64 read, which lets the power-limited clock
-//     run higher. A substep's MFMAs carry the fragment reads of the next
-//     substep and, after the step's barrier, the load issues of the stage
-//     just freed, one every 4 (256x128: 2) MFMAs (bunched issues stall the
-//     single wave of a SIMD on the memory pipeline).
-//   64x64 tiles: 4 waves of 32 x 32, v_mfma_f32_32x32x16 from the compiler's
-//     builtin, loads issued STAGES steps ahead.
-// The main loop is the same for every output pattern (Section 5: only the
-// epilogue changes).
+// issue sits in the shadow of an MFMA. 256x256 and 256x128 tiles: 4 waves of
+// 128 x 128 (128 x 64), one per SIMD, v_mfma_f32_16x16x32 in inline asm with
+// the accumulators tied in place; a wave of 128 x 128 reads 2/3 of the LDS
+// bytes per flop that 8 waves of 128 x 64 read, which lets the power-limited
+// clock run higher. A substep's MFMAs carry the fragment reads of the next
+// substep and, after the step's barrier, the load issues of the stage just
+// freed, one every 4 (256x128: 2) MFMAs (bunched issues stall the single wave
+// of a SIMD on the memory pipeline). The main loop is the same for every
+// output pattern (Section 5: only the epilogue changes). Plans with 64x64
+// tiles run the kernels of gemm_block.hip.
 //
 // Epilogue (Section 3.3 Approach; Section 3.2 Approach):
-//   0. (256x256 form) each row's destination is looked up while the tile's
+//   0. each row's destination is looked up while the tile's
 //      main loop runs, and the next position is claimed a few k steps
 //      before its end;
 //   1. accumulators -> fp16/bf16 (round to nearest even) -> LDS staging tile
@@ -105,28 +102,19 @@ __device__ __forceinline__ void static_for(F&& f) {
     static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
-template <int DT>
-__device__ __forceinline__ f32x16_t mfma32(u32x4_t a, u32x4_t b, f32x16_t c) {
-    if constexpr (DT == FO_FP16)
-        return __builtin_amdgcn_mfma_f32_32x32x16_f16(bit_cast<half8_t>(a), bit_cast<half8_t>(b), c, 0, 0, 0);
-    else
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(bit_cast<bf16x8_t>(a), bit_cast<bf16x8_t>(b), c, 0, 0, 0);
-}
-
-// LDS plan of one workgroup. An operand tile row holds the BK k values of
-// one row of A (or of W): BK * 2 bytes = BK / 8 chunks of 16 bytes; chunk c
-// of row r is stored at slot c ^ ((r >> kSwz) % (BK / 8)). The gfx950 LDS
+// LDS plan of one workgroup. An operand tile row holds 64 k values of one row
+// of A (or of W): 128 bytes = 8 chunks of 16 bytes; chunk c of row r is stored
+// at slot c ^ ((r >> kSwz) % 8). The gfx950 LDS
 // serves a 16-byte read for 16 lanes per cycle across 64 banks (256 bytes):
-// 256 / (BK * 2) consecutive rows share a 256-byte bank line, so the 16 rows
+// two consecutive rows share a 256-byte bank line, so the 16 rows
 // read together at one k position must land in 16 different (row within the
-// line, slot) pairs, which this swizzle gives for any 16 consecutive rows
-// (BK = 64: pairs of rows, shift 1; BK = 32: quads of rows, shift 2).
-template <int BM, int BN, int STAGES, int NW, int BK>
+// line, slot) pairs, which this swizzle gives for any 16 consecutive rows.
+template <int BM, int BN, int STAGES, int NW>
 struct Tiles {
-    static constexpr int kBK = BK;                       // k values per main-loop step
-    static constexpr int kRow = BK * 2;                  // bytes per operand row
-    static constexpr int kCh = BK / 8;                   // 16-byte chunks per row
-    static constexpr int kSwz = BK == 64 ? 1 : 2;        // log2(rows per bank line)
+    static constexpr int kBK = 64;                       // k values per main-loop step
+    static constexpr int kRow = kBK * 2;                 // bytes per operand row
+    static constexpr int kCh = kBK / 8;                  // 16-byte chunks per row
+    static constexpr int kSwz = 1;                       // log2(rows per bank line)
     static constexpr int kRowsPerBlk = 1024 / kRow;      // rows per 1 KB load block
     static constexpr int kA = BM * kRow, kB = BN * kRow;
     static constexpr int kStage = kA + kB;
@@ -153,7 +141,7 @@ struct Tiles {
 // w_bytes long; the host checks they fit in 32 bits): a read past them
 // returns zero instead of faulting, and a resource of length 0 loads zeros
 // without touching memory.
-template <int AI, int BI, int KA, bool OPAQUE = true>
+template <int AI, int BI, int KA>
 __device__ __forceinline__ void issue_tile(const uint16_t* Ablk, const uint16_t* Wblk, uint32_t a_bytes,
                                            uint32_t w_bytes, const uint32_t* voffA, const uint32_t* voffB,
                                            uint32_t soff, char* st, int wave) {
@@ -161,13 +149,7 @@ __device__ __forceinline__ void issue_tile(const uint16_t* Ablk, const uint16_t*
         __builtin_amdgcn_make_buffer_rsrc((void*)Ablk, 0, (int)a_bytes, kRsrcWord3);
     const __amdgpu_buffer_rsrc_t rW =
         __builtin_amdgcn_make_buffer_rsrc((void*)Wblk, 0, (int)w_bytes, kRsrcWord3);
-    // The LDS block addresses (one scalar register each, M0 of the load) are
-    // formed here from an opaque copy of the wave index, so that they are
-    // not all kept live through the main loop (OPAQUE; the 4-wave kernel
-    // takes the uniform index directly).
-    int w = wave;
-    if constexpr (OPAQUE) asm volatile("" : "+s"(w));
-    else w = __builtin_amdgcn_readfirstlane(wave);
+    const int w = __builtin_amdgcn_readfirstlane(wave);
 #pragma unroll
     for (int i = 0; i < AI; ++i)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, (lds_void_t*)(st + (w * AI + i) * 1024), 16, voffA[i],
@@ -196,21 +178,6 @@ __device__ __forceinline__ void issue_one(int idx, const uint16_t* Ablk, const u
     }
 }
 
-// Instruction order inside one k-step phase of the main loop: each MFMA
-// (32 cycles of matrix work) carries up to R LDS fragment reads and V
-// direct-to-LDS load issues in its shadow, so the matrix pipe does not
-// drain while they are issued.
-template <int MFMA, int R, int V>
-__device__ __forceinline__ void interleave_phase() {
-    constexpr int r1 = (R + MFMA - 1) / MFMA, v1 = (V + MFMA - 1) / MFMA;
-#pragma unroll
-    for (int i = 0; i < MFMA; ++i) {
-        if (i * r1 < R) __builtin_amdgcn_sched_group_barrier(0x100, r1, 0);   // LDS read
-        if (i * v1 < V) __builtin_amdgcn_sched_group_barrier(0x020, v1, 0);   // global load
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                    // MFMA
-    }
-}
-
 // One main-loop synchronization: this wave waits until at most `vm` of its
 // vector memory operations are in flight (its part of the next tile has
 // landed in LDS) and until all of its LDS reads have returned (the stage it
@@ -227,27 +194,25 @@ __device__ __forceinline__ void wait_and_barrier() {
     asm volatile("" ::: "memory");
 }
 
-// The kernel body; MF = 32 (v_mfma_f32_32x32x16, compiler builtin) or 16
-// (v_mfma_f32_16x16x32 in tied inline asm, two stages of 64-wide k steps).
-template <int DT, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int BK, int MF>
+// The kernel body: v_mfma_f32_16x16x32 in tied inline asm, two stages of
+// 64-wide k steps.
+template <int DT, int BM, int BN, int WAVES_M, int WAVES_N>
 __device__ __forceinline__ void gemm_body(const GemmArgs& a) {
+    constexpr int MF = 16, STAGES = 2;
     constexpr int NW = WAVES_M * WAVES_N, NT = 64 * NW;
     constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
     constexpr int MI = WTM / MF, NJ = WTN / MF;
-    constexpr int KPM = 512 / MF;                        // k per MFMA: 16 (32x32) or 32 (16x16)
-    using AccT = typename std::conditional<MF == 32, f32x16_t, f32x4_t>::type;
-    constexpr int NACC = MF == 32 ? 16 : 4;              // accumulator registers per block and lane
-    constexpr int kVRows = MF == 16 ? 2 : 0;             // accumulator block rows held in VGPRs
-    using T = Tiles<BM, BN, STAGES, NW, BK>;
+    constexpr int KPM = 512 / MF;                        // k per MFMA
+    using AccT = f32x4_t;
+    constexpr int NACC = 4;                              // accumulator registers per block and lane
+    constexpr int kVRows = 2;                            // accumulator block rows held in VGPRs
+    using T = Tiles<BM, BN, STAGES, NW>;
     constexpr int kBK = T::kBK;
-    constexpr int P = kBK / KPM;                         // MFMA k steps per main-loop step
-    static_assert(NW == 4 || NW == 8, "four or eight waves");
+    constexpr int P = kBK / KPM;                         // MFMA k steps (substeps) per main-loop step
+    static_assert(NW == 4, "four waves");
     static_assert(NT >= BM, "one thread per tile row in the epilogue set-up");
-    static_assert(MF == 32 || MF == 16, "32x32x16 or 16x16x32 MFMAs");
     static_assert(WTM % MF == 0 && WTN % MF == 0, "whole MFMA blocks");
-    static_assert(MF == 32 || (STAGES == 2 && P == 2), "the 16x16x32 form runs two stages of 64-wide k steps");
-    static_assert(STAGES >= 2 && STAGES <= 4, "two to four LDS stages");
-    static_assert(BK == 32 || BK == 64, "k steps of 32 or 64");
+    static_assert(P == 2, "two substeps per step");
     static_assert(T::kAI >= 1 && T::kBI >= 1 && T::kA % (1024 * NW) == 0 && T::kB % (1024 * NW) == 0,
                   "each wave loads whole 1 KB blocks");
     static_assert(T::kRowsPerPass <= T::kCap, "output staging fits in the stages");
@@ -257,8 +222,6 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a) {
     // stage being read from the stages being filled.
     __shared__ __attribute__((aligned(1024))) char st0[T::kStage];
     __shared__ __attribute__((aligned(1024))) char st1[T::kStage];
-    __shared__ __attribute__((aligned(STAGES >= 3 ? 1024 : 16))) char st2[STAGES >= 3 ? T::kStage : 16];
-    __shared__ __attribute__((aligned(STAGES >= 4 ? 1024 : 16))) char st3[STAGES >= 4 ? T::kStage : 16];
     __shared__ int64_t row_off[BM];
     __shared__ int s_pos;
 
@@ -324,7 +287,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a) {
     // same loads and the wait counts stay uniform (no branches).
     auto issue = [&](int kt, char* st) {
         const bool live = kt < KT;
-        issue_tile<T::kAI, T::kBI, T::kA, MF == 32>(Ablk, Wblk, live ? (uint32_t)(BM * K * 2) : 0u,
+        issue_tile<T::kAI, T::kBI, T::kA>(Ablk, Wblk, live ? (uint32_t)(BM * K * 2) : 0u,
                                          live ? (uint32_t)(BN * K * 2) : 0u, voffA, voffB,
                                          live ? (uint32_t)kt * (kBK * 2) : 0u, st, wave);
     };
@@ -353,39 +316,28 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a) {
         for (int j = 0; j < NJ; ++j)
             fb[j] = *reinterpret_cast<const u32x4_t*>(st + b_row + j * MF * T::kRow + cslot[kk]);
     };
-    // W fragment as the MFMA's first operand: the result block is C^T, so
-    // each lane holds 4 consecutive output columns.
-    auto mma = [&](const u32x4_t (&fa)[MI], const u32x4_t (&fb)[NJ]) {
-        if constexpr (MF == 32) {
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                for (int j = 0; j < NJ; ++j)
-                    acc[i][j] = mfma32<DT>(fb[j], fa[i], acc[i][j]);
-        }
-    };
-
-    constexpr int kMfma = MI * NJ, kReads = MI + NJ;
-    // 16x16x32 form: destination of tile row `tid` (element offset), looked
+    // Destination of tile row `tid` (element offset), looked
     // up at the start of the tile and written to row_off after the first
     // main-loop barrier, so that the lookups' latency hides under the loop
     // (the previous tile's epilogue is done with row_off by then).
     int64_t my_off = 0;
     // Group of the previous tile whose count is still to be sent (or -1):
-    // with device-coherent stores and two stages, a tile's count goes out at
+    // with device-coherent stores, a tile's count goes out at
     // the first main-loop barrier of the workgroup's next tile, so that the
     // stores complete while the next tile's first loads are in flight.
     int pend = -1;
     constexpr std::true_type kYes{};
     constexpr std::false_type kNo{};
-    const bool defer = STAGES == 2 && coherent && !a.trace;
+    const bool defer = coherent && !a.trace;
     // Step kt multiplies the tile in stage `cur` (its k step 0 fragments are
     // already in fa0/fb0; tile kt+1 is in stage `nxt`). Before its last k
     // step, every wave has read all of `cur` and tile kt+1 has landed (tiles
     // up to kt+STAGES-1 may still be loading): after the barrier, tile
     // kt+STAGES goes into `cur`, and the first fragments of tile kt+1 are read
     // while the last MFMAs of tile kt run.
-    // 16x16x32 form: MFMA m of a substep (block row m / NJ, column m % NJ)
+    // The W fragment is the MFMA's first operand: the result block is C^T, so
+    // each lane holds 4 consecutive output columns.
+    // MFMA m of a substep (block row m / NJ, column m % NJ)
     // carries fragment read m of the next substep (m < MI + NJ: A0, B0 ..
     // B(NJ-1), A1 .. A(MI-1), the order the next substep needs them) and, in
     // the substep after the barrier, every 4th MFMA one load issue of the
@@ -420,51 +372,19 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a) {
         });
     };
     auto step = [&](int kt, char* cur, const char* nxt, auto first_c) __attribute__((always_inline)) {
-        if constexpr (MF == 16) {
-            mma_rd(fa0, fb0, cur, 1, fa1, fb1, 0, cur, false, first_c);
-            wait_and_barrier<0>();
-            if constexpr (decltype(first_c)::value) {
-                // the previous tile's stores are complete in every wave (this
-                // barrier follows a vmcnt(0) wait): its deferred count goes out
-                if (pend >= 0) {
-                    if (tid == 0)
-                        __hip_atomic_fetch_add(a.counters + pend, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    pend = -1;
-                }
-                if (tid < BM) row_off[tid] = my_off;
-            }
-            mma_rd(fa1, fb1, nxt, 0, fa0, fb0, kt + STAGES, cur, true, std::false_type{});
-            return;
-        }
-        load_frags(cur, 1, fa1, fb1);
-        mma(fa0, fb0);
-        interleave_phase<kMfma, kReads, 0>();
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (P == 4) {
-            load_frags(cur, 2, fa0, fb0);
-            mma(fa1, fb1);
-            interleave_phase<kMfma, kReads, 0>();
-            __builtin_amdgcn_sched_barrier(0);
-            load_frags(cur, 3, fa1, fb1);
-            mma(fa0, fb0);
-            interleave_phase<kMfma, kReads, 0>();
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        wait_and_barrier<(STAGES - 2) * T::kLoads>();
-        if constexpr (STAGES == 2 && decltype(first_c)::value) {
-            // The previous tile's stores are complete in every wave (this
-            // barrier follows a vmcnt(0) wait): its deferred count goes out.
+        mma_rd(fa0, fb0, cur, 1, fa1, fb1, 0, cur, false, first_c);
+        wait_and_barrier<0>();
+        if constexpr (decltype(first_c)::value) {
+            // the previous tile's stores are complete in every wave (this
+            // barrier follows a vmcnt(0) wait): its deferred count goes out
             if (pend >= 0) {
                 if (tid == 0)
                     __hip_atomic_fetch_add(a.counters + pend, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 pend = -1;
             }
+            if (tid < BM) row_off[tid] = my_off;
         }
-        issue(kt + STAGES, cur);
-        load_frags(nxt, 0, fa0, fb0);
-        mma(fa1, fb1);
-        interleave_phase<kMfma, kReads, T::kLoads>();
-        __builtin_amdgcn_sched_barrier(0);
+        mma_rd(fa1, fb1, nxt, 0, fa0, fb0, kt + STAGES, cur, true, std::false_type{});
     };
 
     // Column n (a multiple of 4 halfs) of staging row r of an output pass
@@ -473,7 +393,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a) {
     auto cptr = [&](int r, int n) -> uint16_t* {
         constexpr int RPS = T::kRowsPerStage;
         const int si = r / RPS, rr = r - (r / RPS) * RPS;
-        char* base = si == 0 ? st0 : si == 1 ? st1 : si == 2 ? st2 : st3;
+        char* base = si == 0 ? st0 : st1;
         const int chunk = (n >> 3) ^ (r & (T::kCCh - 1));
         return reinterpret_cast<uint16_t*>(base + rr * T::kLDC * 2 + chunk * 16 + (n & 7) * 2);
     };
@@ -513,63 +433,31 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a) {
             }
             return off;
         };
-        if constexpr (MF == 32) {      // (the 16x16x32 form starts them with srcC = 0)
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                for (int j = 0; j < NJ; ++j)
-#pragma unroll
-                    for (int r = 0; r < NACC; ++r) acc[i][j][r] = 0.0f;
-        }
-
         issue(0, st0);
         issue(1, st1);
-        if constexpr (MF == 16)
-            if (tid < BM) my_off = row_dest(tid);
-        if constexpr (STAGES >= 3) issue(2, st2);
-        if constexpr (STAGES >= 4) issue(3, st3);
+        if (tid < BM) my_off = row_dest(tid);
         wait_and_barrier<(STAGES - 1) * T::kLoads>();
         load_frags(st0, 0, fa0, fb0);
         int kt = 0;
         bool claimed = false;
         int next = p + (int)gridDim.x;
-        if constexpr (STAGES == 4) {
-            for (; kt + 4 <= KT; kt += 4) {      // tile t lives in stage t % 4
-                step(kt, st0, st1, kNo);
-                step(kt + 1, st1, st2, kNo);
-                step(kt + 2, st2, st3, kNo);
-                step(kt + 3, st3, st0, kNo);
+        // tile t lives in stage t % 2; the first step sends the previous
+        // tile's deferred count
+        step(0, st0, st1, kYes);
+        for (kt = 1; kt + 2 <= KT; kt += 2) {
+            // the next position is claimed two to three steps before the end
+            // of this tile, so that the atomic's latency hides under them
+            if (a.dispenser && !claimed && kt + 4 >= KT) {
+                claimed = true;
+                if (tid == 0) next = claim();
             }
-            if (kt < KT) step(kt, st0, st1, kNo);
-            if (kt + 1 < KT) step(kt + 1, st1, st2, kNo);
-            if (kt + 2 < KT) step(kt + 2, st2, st3, kNo);
-        } else if constexpr (STAGES == 3) {
-            for (; kt + 3 <= KT; kt += 3) {      // tile t lives in stage t % 3
-                step(kt, st0, st1, kNo);
-                step(kt + 1, st1, st2, kNo);
-                step(kt + 2, st2, st0, kNo);
-            }
-            if (kt < KT) step(kt, st0, st1, kNo);
-            if (kt + 1 < KT) step(kt + 1, st1, st2, kNo);
-        } else {                                 // tile t lives in stage t % 2
-            // the first step sends the previous tile's deferred count
-            step(0, st0, st1, kYes);
-            for (kt = 1; kt + 2 <= KT; kt += 2) {
-                // 16x16x32 form: the next position is claimed two to three
-                // steps before the end of this tile, so that the atomic's
-                // latency hides under them
-                if (MF == 16 && a.dispenser && !claimed && kt + 4 >= KT) {
-                    claimed = true;
-                    if (tid == 0) next = claim();
-                }
-                step(kt, st1, st0, kNo);
-                step(kt + 1, st0, st1, kNo);
-            }
-            if (kt < KT) step(kt, st1, st0, kNo);
+            step(kt, st1, st0, kNo);
+            step(kt + 1, st0, st1, kNo);
         }
+        if (kt < KT) step(kt, st1, st0, kNo);
         // inline-asm MFMAs: the accumulators are read only once the last
         // MFMA's result is written (the compiler inserts no wait for them)
-        if constexpr (MF == 16) asm volatile("s_nop 7\n s_nop 7\n s_nop 7\n s_nop 7" ::: "memory");
+        asm volatile("s_nop 7\n s_nop 7\n s_nop 7\n s_nop 7" ::: "memory");
         wait_and_barrier<0>();    // no load may still be writing LDS
         __syncthreads();          // operand stages are reused for the output tile
 
@@ -582,9 +470,6 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a) {
         asm volatile("" : "+v"(tid_e));
         const int lane_e = tid_e & 63, wave_e = __builtin_amdgcn_readfirstlane(tid_e >> 6);
         const int wm_e = wave_e / WAVES_N, wn_e = wave_e % WAVES_N;
-        // Destination of row `tid` of the tile, by pattern.
-        if (MF != 16 && tid < BM) row_off[tid] = row_dest(tid);
-
         // Otherwise the next position is claimed now; the atomic's latency
         // hides behind this tile's stores.
         if (a.dispenser && !claimed && tid == 0) next = claim();
@@ -593,7 +478,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a) {
         for (int pass = 0; pass < T::kPasses; ++pass) {
             const int r0 = pass * T::kRowsPerPass;
             // accumulators of the waves whose rows are in this pass -> staging
-            if constexpr (MF == 16 && BN == 256) {
+            if constexpr (BN == 256) {
                 // 256 x 256 tile, 4 waves of 128 x 128, one pass: the
                 // addresses of cptr in closed form. Lane l of block (i, j)
                 // holds tile row wm*128 + i*16 + l%16, columns wn*128 + j*16 +
@@ -651,7 +536,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a) {
                 constexpr int CPR = BN / 8;             // 16-byte chunks per tile row
                 constexpr int RPP = NT / CPR;           // rows per pass of the workgroup
                 const int c = tid_e % CPR;
-                if constexpr (MF == 16 && BN == 256) {
+                if constexpr (BN == 256) {
                     // thread t stores chunk c of tile rows r = t/32 + 8k
                     // (k < 32): stage k/16, staging row r % 128, chunk
                     // c ^ (r % 32) = c ^ (t/32 + 8 (k % 4))
@@ -768,31 +653,20 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a) {
     }
 }
 
-template <int DT, int BM, int BN, int WM, int WN, int ST, int BK>
-__global__ __launch_bounds__(64 * WM * WN, 1) void gemm_signal_kernel(const GemmArgs a) {
-    gemm_body<DT, BM, BN, WM, WN, ST, BK, 32>(a);
-}
-
 // 256x256 tiles, 4 waves of 128x128 (16x16x32 MFMAs). At most 216 VGPRs
 // (two accumulator block rows among them, the rest of the accumulators in
 // AGPRs): the wave leaves 64 of the SIMD's 512 registers per lane to a
 // consumer wave, which can therefore run beside it.
 template <int DT>
 __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_num_vgpr(216))) void gemm_w4_kernel(const GemmArgs a) {
-    gemm_body<DT, 256, 256, 2, 2, 2, 64, 16>(a);
+    gemm_body<DT, 256, 256, 2, 2>(a);
 }
 
 // 256x128 tiles, 4 waves of 128x64 (16x16x32 MFMAs; 128 accumulator
 // registers per lane, no register cap needed).
 template <int DT>
 __global__ __launch_bounds__(256, 1) void gemm_w4n_kernel(const GemmArgs a) {
-    gemm_body<DT, 256, 128, 2, 2, 2, 64, 16>(a);
-}
-
-template <int DT, int BM, int BN, int WM, int WN, int ST, int BK>
-hipError_t launch_t(const GemmArgs& a, int grid, hipStream_t s) {
-    hipLaunchKernelGGL((gemm_signal_kernel<DT, BM, BN, WM, WN, ST, BK>), dim3(grid), dim3(64 * WM * WN), 0, s, a);
-    return hipGetLastError();
+    gemm_body<DT, 256, 128, 2, 2>(a);
 }
 
 template <int DT>
@@ -811,9 +685,6 @@ hipError_t launch_gemm(int dtype, int tile_m, int tile_n, const GemmArgs& a, int
     }
     if (tile_m == 256 && tile_n == 256)
         return dtype == FO_FP16 ? launch_w4<FO_FP16>(a, grid, s) : launch_w4<FO_BF16>(a, grid, s);
-    if (tile_m == 64 && tile_n == 64)
-        return dtype == FO_FP16 ? launch_t<FO_FP16, 64, 64, 2, 2, 3, 64>(a, grid, s)
-                                : launch_t<FO_BF16, 64, 64, 2, 2, 3, 64>(a, grid, s);
     return hipErrorInvalidValue;
 }
 

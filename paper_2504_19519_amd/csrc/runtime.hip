@@ -354,7 +354,10 @@ fo_status fo_gemm_signal_reorder(const fo_plan* plan, const void* dev_plan, cons
         a.num_dispensers = plan->order == FO_ORDER_XCD ? std::min(plan->num_xcds, FO_DISPENSER_WORDS) : 1;
         a.num_dispensers = std::max(1, std::min(a.num_dispensers, grid));
     }
-    hipError_t e = fo::launch_gemm(plan->dtype, plan->tile_m, plan->tile_n, a, grid, (hipStream_t)stream);
+    hipError_t e = plan->tile_m == 64
+                       ? fo::launch_gemm64(plan->dtype, a, std::max(plan->W, 1), plan->reserved_cus == 0,
+                                             (hipStream_t)stream)
+                       : fo::launch_gemm(plan->dtype, plan->tile_m, plan->tile_n, a, grid, (hipStream_t)stream);
     return e == hipSuccess ? FO_OK : fo::hip_fail("GEMM launch", e);
 }
 

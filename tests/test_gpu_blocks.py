@@ -1,0 +1,58 @@
+"""The block forms of plans with 64x64 tiles, on the GPU.
+
+The GEMM of such a plan computes 128x128, 64x64, 64x32 or 32x32 outputs per
+workgroup, chosen by the number of tiles against the plan's wave width (parts
+of a tile only without counters). Every form must give the same bits, at the
+edges of the rule, with an odd number of tile rows and columns (128x128 blocks
+that reach past the output) and every remainder of the k steps.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2504_19519_amd as fo
+import workloads
+from gpu_util import assert_close_bits, dev_plan, empty16, from_dev, say, to_dev, torch_mod, zeros_u32
+
+pytestmark = pytest.mark.gpu
+
+M, N = 192, 320          # 15 tiles
+# W = modelled compute units: 15 tiles <= W/4, > W/4, <= W/2, > W/2, <= 2 W, > 2 W
+WIDTHS = [60, 59, 30, 29, 8, 7]
+
+
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("K", [64, 128, 192, 448, 640])
+def test_block_forms(dtype, K):
+    torch = torch_mod()
+    say(f"[gemm blocks] {M}x{N}x{K} {dtype}")
+    rng = np.random.default_rng(K)
+    A = workloads.to_bits(rng.uniform(-1, 1, (M, K)), dtype)
+    W = workloads.to_bits(rng.uniform(-1, 1, (N, K)) / np.sqrt(K), dtype)
+    dA, dW = to_dev(A), to_dev(W)
+    plain = None
+    for cus in WIDTHS:
+        for pattern, nd in [("rowmajor", 0), ("tile", 0), ("subtile", 4), ("subtoken", 3)]:
+            sigma = rng.permutation(nd) if pattern == "subtile" else None
+            bucket = rng.integers(0, nd, M) if pattern == "subtoken" else None
+            T = -(-15 // cus)
+            sizes = [1] * T
+            plan = fo.plan_groups(M, N, K, dtype=dtype, tile_m=64, tile_n=64, num_cus=cus, pattern=pattern,
+                                  num_dest=nd, dest_perm=sigma, row_bucket=bucket, sizes=sizes)
+            o = oracle.make_plan(M, N, 64, 64, num_cus=cus, order="xcd", group_m=4, num_xcds=8, pattern=pattern,
+                                 num_dest=nd, sigma=sigma, bucket=bucket, sizes=sizes, unit="waves")
+            dp = dev_plan(plan)
+            for counters in (None, zeros_u32(plan.num_counters)):
+                C = empty16(M * N, dtype)
+                fo.gemm_signal_reorder(plan, dp, dA, dW, C, counters)
+                torch.cuda.synchronize()
+                got = from_dev(C)[:M * N]
+                if plain is None:
+                    plain = got
+                    assert_close_bits(got, oracle.gemm_ref(A, W, dtype).reshape(-1), dtype, "GEMM")
+                what = f"W={cus} {pattern} {'signalled' if counters is not None else 'unsignalled'}"
+                np.testing.assert_array_equal(got, plain[oracle.reorder_index(o)], err_msg=what)
+                if counters is not None:
+                    c = counters.cpu().numpy()
+                    np.testing.assert_array_equal(c[:plan.P], np.array(o.targets), err_msg=what)
+                    np.testing.assert_array_equal(c[plan.P:plan.P + fo.DISPENSER_WORDS], 0, err_msg=what)
