@@ -426,7 +426,10 @@ fo_status fo_reset_counters(uint32_t* counters, int32_t n, void* stream);
  * on gemm_stream, without the handoffs and without signalling. A plan of one
  * group has nothing to overlap (its consumer can only start after the whole
  * GEMM): with a comm_stream it runs serialized on gemm_stream too, the same
- * way (counters untouched). An overlapped run needs counters and,
+ * way (counters untouched). A serialized run with an out consumes and restores
+ * in one kernel (the same values in dst and out) unless the consumers are
+ * capped, out overlaps C_out or peer, or peer is not 16-byte aligned. An
+ * overlapped run needs counters and,
  * with more than one group, a created gemm_stream (not the null stream,
  * which would wait for the gate kernel on a blocking comm_stream).
  * The overlap also needs the two streams on different hardware queues: HIP

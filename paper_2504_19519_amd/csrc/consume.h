@@ -70,6 +70,20 @@ __host__ __device__ inline uint32_t done_tag_of(uint32_t seq) { return (seq & 0x
 __host__ __device__ inline uint32_t done_share(int32_t blocks, int k) {
     return blocks > k ? (uint32_t)((blocks - 1 - k) / kDoneWords + 1) : 0u;
 }
+#if defined(__HIPCC__)
+// One finished workgroup of the final launch (its stores complete), counted for
+// its own run only: once a later run's reset has put its tag into the word, a
+// late workgroup leaves it alone. (A plain add after the check: a
+// compare-and-swap loop would serialise the grid's workgroups on one word,
+// about a microsecond each. A late workgroup can only race with a later run's
+// reset if an earlier wait of the stream pair timed out, which the sticky
+// status bit already reports.)
+__device__ __forceinline__ void count_done(uint32_t* done, uint32_t done_tag) {
+    uint32_t* w = done + (blockIdx.x % kDoneWords) * kDoneStride;
+    const uint32_t v = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((v & 0xFFFF0000u) == done_tag) __hip_atomic_fetch_add(w, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+#endif
 // One wave that polls the done words until word k reaches done_tag plus
 // done_share(blocks, k) for every k (bounded like launch_wait).
 hipError_t launch_done_wait(const uint32_t* done, uint32_t done_tag, int32_t blocks, uint32_t* status,

@@ -168,24 +168,6 @@ __device__ __forceinline__ bool check_counter(const uint32_t* counter, uint32_t 
 }
 
 template <int DT>
-__device__ __forceinline__ u32x4_t add8(u32x4_t x, u32x4_t y) {
-    u32x4_t r;
-    if constexpr (DT == FO_FP16) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            r[e] = bit_cast<uint32_t>(bit_cast<half2_t>(x[e]) + bit_cast<half2_t>(y[e]));
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float lo = bf16_bits_to_f32(x[e] & 0xFFFFu) + bf16_bits_to_f32(y[e] & 0xFFFFu);
-            const float hi = bf16_bits_to_f32(x[e] >> 16) + bf16_bits_to_f32(y[e] >> 16);
-            r[e] = pack2<FO_BF16>(lo, hi);
-        }
-    }
-    return r;
-}
-
-template <int DT>
 __device__ __forceinline__ uint16_t add1(uint16_t x, uint16_t y) {
     return (uint16_t)from_f32<DT>(to_f32<DT>(x) + to_f32<DT>(y));
 }
@@ -370,19 +352,7 @@ __global__ __launch_bounds__(kMaxThreads) void consume_kernel(const ConsumeArgs 
     if constexpr (WT) {
         __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
         __syncthreads();
-        if (threadIdx.x == 0) {
-            // Count only for this launch's own run: once a later run's reset
-            // has put its tag into the word, a late workgroup leaves it alone.
-            // (A plain add after the check: a compare-and-swap loop would
-            // serialise the grid's workgroups on one word, about a
-            // microsecond each. A late workgroup can only race with a later
-            // run's reset if an earlier wait of the stream pair timed out,
-            // which the sticky status bit already reports.)
-            uint32_t* w = a.done + (blockIdx.x % kDoneWords) * kDoneStride;
-            const uint32_t v = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if ((v & 0xFFFF0000u) == a.done_tag)
-                __hip_atomic_fetch_add(w, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        if (threadIdx.x == 0) count_done(a.done, a.done_tag);
     }
 }
 

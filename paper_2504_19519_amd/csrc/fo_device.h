@@ -68,4 +68,23 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {
     else return bit_cast<uint32_t>(__builtin_convertvector(v, bf16x2_t));
 }
 
+// Eight sums of two 16-bit values, each rounded once (to nearest even).
+template <int DT>
+__device__ __forceinline__ u32x4_t add8(u32x4_t x, u32x4_t y) {
+    u32x4_t r;
+    if constexpr (DT == 0) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            r[e] = bit_cast<uint32_t>(bit_cast<half2_t>(x[e]) + bit_cast<half2_t>(y[e]));
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float lo = bf16_bits_to_f32(x[e] & 0xFFFFu) + bf16_bits_to_f32(y[e] & 0xFFFFu);
+            const float hi = bf16_bits_to_f32(x[e] >> 16) + bf16_bits_to_f32(y[e] >> 16);
+            r[e] = pack2<1>(lo, hi);
+        }
+    }
+    return r;
+}
+
 }  // namespace fo

@@ -24,11 +24,34 @@ struct PostArgs {
     const int32_t* pool_off;
     float eps;
     int32_t do_norm;
+    // The fused form is the consumer as well: it reads the GEMM's output (and
+    // the peer's partial, if any), each of `bytes`, and fills src itself.
+    const uint16_t* gemm_out;
+    const uint16_t* peer;
+    uint32_t bytes;
+    const int32_t* slot_group;
+    const int32_t* group_first;
 };
 
-// LDS bytes one post-reorder workgroup uses (source piece offsets of its 4
-// rows; bias and gamma chunks when the row is normalised in registers).
-size_t post_lds_bytes(const PostArgs& a);
-hipError_t launch_post(int dtype, const PostArgs& a, hipStream_t s);
+// The kernel form of a launch.
+struct PostForm {
+    int32_t waves_per_row;      // 1 or 4
+    int32_t chunks;             // 16-byte chunks of a row per lane; 0: rows read twice; -1: plain restore
+    uint32_t blocks;
+    size_t lds;                 // bytes per workgroup
+};
+constexpr size_t kMaxPostLds = 64 * 1024;
+// LDS bytes per workgroup by which a size is accepted or refused, whatever form
+// it then takes: four rows' piece offsets, and bias and gamma of a row of up to
+// 8192 columns.
+inline size_t post_lds_bound(const PostArgs& a) {
+    const bool affine = (a.do_norm || a.bias) && (a.bias || a.gamma) && a.N <= 8192;
+    return 16 * (size_t)a.tiles_n + (affine ? 4 * (size_t)a.N : 0);
+}
+
+PostForm post_form(const PostArgs& a, bool fused);
+// Whether the fused form exists for these sizes.
+bool post_fusable(const PostArgs& a);
+hipError_t launch_post(int dtype, const PostArgs& a, bool fused, hipStream_t s);
 
 }  // namespace fo

@@ -2,8 +2,9 @@
 // (Section 3.3 Approach, last paragraph: the kernel after communication
 // loads by the reordered index; Section 6.6 fuses it with RMSNorm).
 //
-// One wave per output row, four rows per workgroup. Lane l handles the
-// 16-byte chunks l, l+64, ... of the row. A chunk lies inside one tile
+// One wave per output row and four rows per workgroup, or a workgroup per row
+// (post_form). A lane handles every 64th (256th) 16-byte chunk of the row. A
+// chunk lies inside one tile
 // column, so its source is 16 contiguous bytes of one row piece: the row's
 // place in that tile's slot (tile pattern), in the slice's destination
 // buffer (subtile pattern) or in the row's pool (subtoken pattern), and
@@ -19,10 +20,14 @@
 //                       in flight before their stores;
 //   post_norm_kernel    bias add and/or RMSNorm: the row is loaded up front
 //                       and held in registers between the sum-of-squares and
-//                       the scaling (rows up to 8192 wide, bias and gamma
-//                       copied to LDS), or read twice for wider rows; which
-//                       of bias, RMSNorm and gamma run is a compile-time
-//                       choice.
+//                       the scaling (rows up to 16384 wide; bias and gamma in
+//                       LDS where four rows share them), or read twice for
+//                       wider rows; which of bias, RMSNorm and gamma run is a
+//                       compile-time choice.
+// Each also in a fused form that is the consumer as well, for runs on one
+// stream: it reads the GEMM's output and the peer's partial and writes the
+// consumer's buffer and the output. Both are bound by memory: 8192x8192
+// restore 52 us and fused 89 us (5.2 and 6.0 TB/s; a large copy reaches 5.1).
 // Sources are read through the caches (the consumer has just written them,
 // so part of them is still in the memory-side cache); the output is written
 // nontemporal.
@@ -36,8 +41,8 @@ namespace fo {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kRowsPerBlock = kThreads / 64;
-constexpr int kMaxRegChunks = 64 * 16;     // rows held in registers: up to 8192 columns
+constexpr int kRsrcWord3 = 0x00020000;      // raw byte-addressed buffer accesses
+constexpr int kSc1Nt = 16 | 2;              // cache policy: device-coherent and nontemporal
 
 typedef __attribute__((address_space(3))) char lds_char_t;
 typedef __attribute__((address_space(3))) uint32_t lds_u32_t;
@@ -52,102 +57,179 @@ __device__ __forceinline__ void widen8(u32x4_t v, float* f) {
     }
 }
 
-// Offset, in 16-byte chunks of the consumer's buffer, of the tile_n-wide
-// source piece of output row i in tile column tn.
-__device__ __forceinline__ uint32_t piece_offset(const PostArgs& a, int64_t i, int tn) {
+// Where the tile_n-wide piece of output row i in tile column tn lies, in
+// 16-byte chunks: [0] in the consumer's buffer; [1] (FUSE) in the GEMM's output
+// and the peer's partial.
+template <bool FUSE>
+__device__ __forceinline__ u32x2_t piece_offset(const PostArgs& a, int64_t i, int tn) {
     const int64_t tw = a.tile_n;
-    if (a.pattern == FO_PATTERN_ROWMAJOR) return (uint32_t)((i * a.N + tn * tw) >> 3);
-    const int32_t tm = (int32_t)(i / a.tile_m);
-    const int32_t r = (int32_t)(i - (int64_t)tm * a.tile_m);
-    const int64_t slot = a.tile_to_slot[(int64_t)tm * a.tiles_n + tn];
-    int64_t off;
-    if (a.pattern == FO_PATTERN_TILE) {
-        off = (slot * a.tile_m + r) * tw;
-    } else if (a.pattern == FO_PATTERN_SUBTILE) {
-        const int32_t h = a.tile_m / a.num_dest;
-        const int32_t k = r / h;
-        off = (int64_t)a.dest_perm[k] * a.per_dest + (slot * h + (r - k * h)) * tw;
+    int64_t off, from;
+    if (a.pattern == FO_PATTERN_ROWMAJOR) {
+        off = from = i * a.N + tn * tw;
     } else {
-        const int32_t b = a.row_bucket[i];
-        off = ((int64_t)a.pool_off[b] + a.pool_base[slot * a.num_dest + b] + a.row_rank[i]) * tw;
+        const int32_t tm = (int32_t)(i / a.tile_m);
+        const int32_t r = (int32_t)(i - (int64_t)tm * a.tile_m);
+        const int64_t slot = a.tile_to_slot[(int64_t)tm * a.tiles_n + tn];
+        if (a.pattern == FO_PATTERN_TILE) {
+            off = from = (slot * a.tile_m + r) * tw;
+        } else if (a.pattern == FO_PATTERN_SUBTILE) {
+            const int32_t h = a.tile_m / a.num_dest;
+            const int32_t k = r / h;
+            off = (int64_t)a.dest_perm[k] * a.per_dest + (slot * h + (r - k * h)) * tw;
+            if constexpr (FUSE) {
+                const int32_t j = a.slot_group[slot];
+                const int64_t f0 = a.group_first[j], nj = a.group_first[j + 1] - f0;
+                from = f0 * a.tile_m * tw + ((k * nj + (slot - f0)) * h + (r - k * h)) * tw;
+            }
+        } else {
+            const int32_t b = a.row_bucket[i];
+            off = from = ((int64_t)a.pool_off[b] + a.pool_base[slot * a.num_dest + b] + a.row_rank[i]) * tw;
+        }
     }
-    return (uint32_t)(off >> 3);
+    u32x2_t p;
+    p[0] = (uint32_t)(off >> 3);
+    p[1] = FUSE ? (uint32_t)(from >> 3) : 0u;
+    return p;
 }
 
-// Source pieces of the workgroup's rows i0 .. i0+3: bases[w * tiles_n + tn].
-__device__ __forceinline__ void stage_pieces(const PostArgs& a, lds_u32_t* bases, int64_t i0) {
-    const int n = kRowsPerBlock * a.tiles_n;
-    for (int idx = threadIdx.x; idx < n; idx += kThreads) {
-        const int w = idx / a.tiles_n, tn = idx - (idx / a.tiles_n) * a.tiles_n;
-        const int64_t i = i0 + w;
-        if (i < a.M) bases[idx] = piece_offset(a, i, tn);
+// What a workgroup knows about its rows: the pieces of rows i0 .. i0 + ROWS - 1
+// in LDS (one word per piece, or two with FUSE).
+template <bool FUSE>
+struct Pieces {
+    lds_u32_t* at;
+    __device__ __forceinline__ void stage(const PostArgs& a, int64_t i0, int rows) const {
+        const int n = rows * a.tiles_n;
+        for (int idx = threadIdx.x; idx < n; idx += kThreads) {
+            const int w = idx / a.tiles_n, tn = idx - w * a.tiles_n;
+            const int64_t i = i0 + w;
+            if (i < a.M) {
+                const u32x2_t p = piece_offset<FUSE>(a, i, tn);
+                at[FUSE ? 2 * idx : idx] = p[0];
+                if constexpr (FUSE) at[2 * idx + 1] = p[1];
+            }
+        }
+    }
+    // where chunk c of the block's row w lies
+    __device__ __forceinline__ u32x2_t chunk(const PostArgs& a, int w, uint32_t c) const {
+        const uint32_t idx = (uint32_t)w * a.tiles_n + (c >> a.cpt_log2), in = c & ((1u << a.cpt_log2) - 1u);
+        u32x2_t p;
+        if constexpr (FUSE) {
+            p = *reinterpret_cast<__attribute__((address_space(3))) u32x2_t*>(at + 2 * idx);
+            p[1] += in;
+        } else {
+            p[0] = at[idx];
+            p[1] = 0u;
+        }
+        p[0] += in;
+        return p;
+    }
+};
+
+// B chunks of the block's row w: chunk c0 + step t, past the row's end its last
+// chunk (dropped by the caller). FUSE: the chunk is consumed on the way, as
+// the consumer does it: the GEMM's output plus the peer's partial (if any),
+// rounded, which is also what the consumer's buffer gets.
+template <int DT, bool FUSE, int B>
+__device__ __forceinline__ void load_chunks(const PostArgs& a, const Pieces<FUSE>& pieces, int w, int c0, int step,
+                                            int nch, u32x4_t* v) {
+    if constexpr (!FUSE) {
+#pragma unroll
+        for (int t = 0; t < B; ++t) {
+            const int c = c0 + step * t;
+            v[t] = reinterpret_cast<const u32x4_t*>(a.src)[pieces.chunk(a, w, c < nch ? c : nch - 1)[0]];
+        }
+    } else {
+        const __amdgpu_buffer_rsrc_t rc =
+            __builtin_amdgcn_make_buffer_rsrc((void*)a.gemm_out, 0, (int)a.bytes, kRsrcWord3);
+        const u32x4_t* q = reinterpret_cast<const u32x4_t*>(a.peer);
+        u32x4_t* d = const_cast<u32x4_t*>(reinterpret_cast<const u32x4_t*>(a.src));
+        constexpr int S = B < 8 ? B : 8;            // chunks in flight at once
+#pragma unroll
+        for (int b = 0; b < B; b += S) {
+            u32x4_t y[S];
+            uint32_t to[S];
+#pragma unroll
+            for (int t = 0; t < S; ++t) {
+                const int c = c0 + step * (b + t);
+                const u32x2_t p = pieces.chunk(a, w, c < nch ? c : nch - 1);
+                to[t] = p[0];
+                v[b + t] = bit_cast<u32x4_t>(__builtin_amdgcn_raw_buffer_load_b128(rc, (int)(p[1] * 16u), 0, kSc1Nt));
+                if (q) y[t] = __builtin_nontemporal_load(q + p[1]);
+            }
+#pragma unroll
+            for (int t = 0; t < S; ++t) {
+                if (q) v[b + t] = add8<DT>(v[b + t], y[t]);
+                if (c0 + step * (b + t) < nch) __builtin_nontemporal_store(v[b + t], d + to[t]);
+            }
+        }
     }
 }
 
-// Chunk c of the row whose piece offsets are `bases` (tile_n / 8 is a power
-// of two, 1 << cpt_log2).
-__device__ __forceinline__ u32x4_t load_chunk(const PostArgs& a, const lds_u32_t* bases, int64_t c) {
-    const uint32_t cpt_mask = (1u << a.cpt_log2) - 1u;
-    const uint32_t off = bases[(uint32_t)c >> a.cpt_log2] + ((uint32_t)c & cpt_mask);
-    return reinterpret_cast<const u32x4_t*>(a.src)[off];
-}
-
-template <int DT>
+// WPR waves per output row (one, or a whole workgroup), 4 / WPR rows per
+// workgroup.
+template <int DT, int WPR, bool FUSE>
 __global__ __launch_bounds__(kThreads) void post_gather_kernel(const PostArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    lds_u32_t* bases = reinterpret_cast<lds_u32_t*>((lds_char_t*)smem);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int64_t i0 = (int64_t)blockIdx.x * kRowsPerBlock;
-    stage_pieces(a, bases, i0);
+    constexpr int kRows = kThreads / 64 / WPR, kLanes = 64 * WPR;
+    const Pieces<FUSE> pieces{reinterpret_cast<lds_u32_t*>((lds_char_t*)smem)};
+    const int lane = threadIdx.x % kLanes, w = threadIdx.x / kLanes;
+    const int64_t i0 = (int64_t)blockIdx.x * kRows, i = i0 + w;
+    pieces.stage(a, i0, kRows);
     __syncthreads();
-    const int64_t i = i0 + w;
-    if (i >= a.M) return;
-    const lds_u32_t* rb = bases + w * a.tiles_n;
-    const int64_t nch = a.N >> 3;
-    u32x4_t* out4 = reinterpret_cast<u32x4_t*>(a.out + i * a.N);
-    constexpr int B = 16;
-    for (int64_t c0 = lane; c0 < nch; c0 += 64 * B) {
-        u32x4_t v[B];
+    if (i < a.M) {
+        const int nch = (int)(a.N >> 3);
+        constexpr int B = FUSE ? 8 : 16;
+        u32x4_t* out4 = reinterpret_cast<u32x4_t*>(a.out + i * a.N);
+        for (int c0 = lane; c0 < nch; c0 += kLanes * B) {
+            u32x4_t v[B];
+            if constexpr (FUSE) {
+                load_chunks<DT, FUSE, B>(a, pieces, w, c0, kLanes, nch, v);
+            } else {
 #pragma unroll
-        for (int t = 0; t < B; ++t)
-            if (c0 + 64 * t < nch) v[t] = load_chunk(a, rb, c0 + 64 * t);
+                for (int t = 0; t < B; ++t)
+                    if (c0 + kLanes * t < nch)
+                        v[t] = reinterpret_cast<const u32x4_t*>(a.src)[pieces.chunk(a, w, c0 + kLanes * t)[0]];
+            }
 #pragma unroll
-        for (int t = 0; t < B; ++t)
-            if (c0 + 64 * t < nch) __builtin_nontemporal_store(v[t], out4 + c0 + 64 * t);
+            for (int t = 0; t < B; ++t)
+                if (c0 + kLanes * t < nch) __builtin_nontemporal_store(v[t], out4 + c0 + kLanes * t);
+        }
     }
 }
 
 // y = (x + bias) [* rsqrt(mean((x + bias)^2) + eps) * gamma]. NORM, BIAS and
 // GAMMA fix at compile time which parts run (GAMMA only with NORM), so that
-// no per-chunk branch and no value of an unused part holds registers.
-template <int DT, int CH, bool NORM, bool BIAS, bool GAMMA>
+// no per-chunk branch and no value of an unused part holds registers. CH > 0:
+// chunks of the row that a lane holds; CH == 0: the row is read twice.
+template <int DT, int CH, int WPR, bool FUSE, bool NORM, bool BIAS, bool GAMMA>
 __global__ __launch_bounds__(kThreads) void post_norm_kernel(const PostArgs a) {
-    constexpr bool kLdsAffine = (BIAS || GAMMA) && CH > 0;
+    static_assert(CH > 0 || (WPR == 1 && !FUSE), "rows read twice: one wave each, not fused");
+    // bias and gamma in LDS where the workgroup's waves share them
+    constexpr bool kLdsAffine = (BIAS || GAMMA) && CH > 0 && WPR == 1;
+    constexpr int kRows = kThreads / 64 / WPR, kLanes = 64 * WPR;
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    const int64_t nch = a.N >> 3;
+    const int nch = (int)(a.N >> 3);
     // LDS: [bias chunks][gamma chunks] (with kLdsAffine), then the pieces
     lds_u32x4_t* s_bias = reinterpret_cast<lds_u32x4_t*>((lds_char_t*)smem);
     lds_u32x4_t* s_gamma = s_bias + (kLdsAffine ? nch : 0);
-    lds_u32_t* bases = reinterpret_cast<lds_u32_t*>(s_gamma + (kLdsAffine ? nch : 0));
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int64_t i0 = (int64_t)blockIdx.x * kRowsPerBlock;
+    const Pieces<FUSE> pieces{reinterpret_cast<lds_u32_t*>(s_gamma + (kLdsAffine ? nch : 0))};
+    const int lane = threadIdx.x % kLanes, w = threadIdx.x / kLanes;
+    const int64_t i0 = (int64_t)blockIdx.x * kRows, i = i0 + w;
     const u32x4_t* bias4 = reinterpret_cast<const u32x4_t*>(a.bias);
     const u32x4_t* gamma4 = reinterpret_cast<const u32x4_t*>(a.gamma);
     if constexpr (kLdsAffine) {
-        for (int64_t c = threadIdx.x; c < nch; c += kThreads) {
+        for (int c = threadIdx.x; c < nch; c += kThreads) {
             if constexpr (BIAS) s_bias[c] = bias4[c];
             if constexpr (GAMMA) s_gamma[c] = gamma4[c];
         }
     }
-    stage_pieces(a, bases, i0);
+    pieces.stage(a, i0, kRows);
     __syncthreads();
-    const int64_t i = i0 + w;
-    if (i >= a.M) return;
-    const lds_u32_t* rb = bases + w * a.tiles_n;
     u32x4_t* out4 = reinterpret_cast<u32x4_t*>(a.out + i * a.N);
+    __shared__ float s_sum[WPR > 1 ? WPR : 1];
 
     // h = x + bias (fp32, no rounding); sb: where bias chunks are read
-    auto shift = [&](u32x4_t xv, int64_t c, const lds_u32x4_t* sb, float* h) {
+    auto shift = [&](u32x4_t xv, int c, const lds_u32x4_t* sb, float* h) {
         widen8<DT>(xv, h);
         if constexpr (BIAS) {
             float bv[8];
@@ -156,7 +238,7 @@ __global__ __launch_bounds__(kThreads) void post_norm_kernel(const PostArgs a) {
             for (int e = 0; e < 8; ++e) h[e] += bv[e];
         }
     };
-    auto sumsq = [&](u32x4_t xv, int64_t c, const lds_u32x4_t* sb) {
+    auto sumsq = [&](u32x4_t xv, int c, const lds_u32x4_t* sb) {
         float h[8];
         shift(xv, c, sb, h);
         float q = 0.0f;
@@ -164,7 +246,7 @@ __global__ __launch_bounds__(kThreads) void post_norm_kernel(const PostArgs a) {
         for (int e = 0; e < 8; ++e) q += h[e] * h[e];
         return q;
     };
-    auto finish = [&](int64_t c, u32x4_t xv, float inv, const lds_u32x4_t* sb, const lds_u32x4_t* sg, bool live) {
+    auto finish = [&](int c, u32x4_t xv, float inv, const lds_u32x4_t* sb, const lds_u32x4_t* sg) -> u32x4_t {
         float h[8], gv[8];
         shift(xv, c, sb, h);
         if constexpr (GAMMA) widen8<DT>(kLdsAffine ? sg[c] : gamma4[c], gv);
@@ -182,101 +264,154 @@ __global__ __launch_bounds__(kThreads) void post_norm_kernel(const PostArgs a) {
             }
             o[e] = pack2<DT>(y0, y1);
         }
-        if (live) __builtin_nontemporal_store(o, out4 + c);
+        return o;
     };
     auto rsqrt_mean = [&](float ss) {
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off, 64);
+        if constexpr (WPR > 1) {
+            if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = ss;
+            __syncthreads();
+            ss = 0.0f;
+#pragma unroll
+            for (int v = 0; v < WPR; ++v) ss += s_sum[v];
+        }
         return 1.0f / sqrtf(ss / (float)a.N + a.eps);
     };
 
     if constexpr (CH > 0) {
-        // The row is loaded up front. Lanes past the row's end load its last
-        // chunk (no branches around the loads: the array stays in registers)
-        // and drop the result.
-        u32x4_t xc[CH];
+        // (a workgroup per row: i < M always, so its waves meet in rsqrt_mean)
+        if (i < a.M) {
+            // The row is loaded up front. Lanes past the row's end load its
+            // last chunk (no branches around the loads: the array stays in
+            // registers) and drop the result.
+            u32x4_t xc[CH];
+            load_chunks<DT, FUSE, CH>(a, pieces, w, lane, kLanes, nch, xc);
+            float inv = 1.0f;
+            if constexpr (NORM) {
+                float ss = 0.0f;
 #pragma unroll
-        for (int t = 0; t < CH; ++t) {
-            const int64_t c = lane + 64 * t;
-            xc[t] = load_chunk(a, rb, c < nch ? c : nch - 1);
-        }
-        float inv = 1.0f;
-        if constexpr (NORM) {
-            float ss = 0.0f;
+                for (int t = 0; t < CH; ++t) {
+                    const int c = lane + kLanes * t;
+                    const float q = sumsq(xc[t], c < nch ? c : nch - 1, s_bias);
+                    ss += c < nch ? q : 0.0f;
+                    // one bias chunk at a time: the LDS reads are not all hoisted
+                    // to the top, where their values would hold registers
+                    if constexpr (kLdsAffine) asm volatile("" ::: "memory");
+                }
+                inv = rsqrt_mean(ss);
+            }
+            // The scaling pass widens the chunks again and reads bias and gamma
+            // again, through pointers the compiler cannot match with the first
+            // pass's, instead of keeping the first pass's values alive.
+#pragma unroll
+            for (int t = 0; t < CH; ++t) asm volatile("" : "+v"(xc[t]));
+            // The lane index is laundered too, so that the second pass's addresses
+            // are formed here and not kept live through the first pass.
+            const lds_u32x4_t* sb = s_bias;
+            const lds_u32x4_t* sg = s_gamma;
+            int ln = lane;
+            asm volatile("" : "+v"(sb), "+v"(sg), "+v"(ln));
 #pragma unroll
             for (int t = 0; t < CH; ++t) {
-                const int64_t c = lane + 64 * t;
-                const float q = sumsq(xc[t], c < nch ? c : nch - 1, s_bias);
-                ss += c < nch ? q : 0.0f;
-                // one bias chunk at a time: the LDS reads are not all hoisted
-                // to the top, where their values would hold registers
+                const int c = ln + kLanes * t;
+                const u32x4_t o = finish(c < nch ? c : nch - 1, xc[t], inv, sb, sg);
+                if (c < nch) __builtin_nontemporal_store(o, out4 + c);
                 if constexpr (kLdsAffine) asm volatile("" ::: "memory");
             }
-            inv = rsqrt_mean(ss);
-        }
-        // The scaling pass widens the chunks again and reads bias and gamma
-        // again, through pointers the compiler cannot match with the first
-        // pass's, instead of keeping the first pass's values alive.
-#pragma unroll
-        for (int t = 0; t < CH; ++t) asm volatile("" : "+v"(xc[t]));
-        // The lane index is laundered too, so that the second pass's addresses
-        // are formed here and not kept live through the first pass.
-        const lds_u32x4_t* sb = s_bias;
-        const lds_u32x4_t* sg = s_gamma;
-        int ln = lane;
-        asm volatile("" : "+v"(sb), "+v"(sg), "+v"(ln));
-#pragma unroll
-        for (int t = 0; t < CH; ++t) {
-            const int64_t c = ln + 64 * t;
-            finish(c < nch ? c : nch - 1, xc[t], inv, sb, sg, c < nch);
-            if constexpr (kLdsAffine) asm volatile("" ::: "memory");
         }
     } else {
+        if (i >= a.M) return;
+        auto at = [&](int c) { return reinterpret_cast<const u32x4_t*>(a.src)[pieces.chunk(a, w, c)[0]]; };
         float inv = 1.0f;
         if constexpr (NORM) {
             float ss = 0.0f;
-            for (int64_t c = lane; c < nch; c += 64) ss += sumsq(load_chunk(a, rb, c), c, s_bias);
+            for (int c = lane; c < nch; c += 64) ss += sumsq(at(c), c, s_bias);
             inv = rsqrt_mean(ss);
         }
-        for (int64_t c = lane; c < nch; c += 64) finish(c, load_chunk(a, rb, c), inv, s_bias, s_gamma, true);
+        for (int c = lane; c < nch; c += 64)
+            __builtin_nontemporal_store(finish(c, at(c), inv, s_bias, s_gamma), out4 + c);
     }
 }
 
-template <int DT, int CH>
-void launch_norm(const PostArgs& a, dim3 g, dim3 b, hipStream_t s) {
-    const size_t lds = post_lds_bytes(a);
+template <int DT, int CH, int WPR, bool FUSE>
+void launch_norm(const PostArgs& a, dim3 g, size_t lds, hipStream_t s) {
+    const dim3 b(kThreads);
     const bool bias = a.bias != nullptr, gamma = a.do_norm && a.gamma != nullptr;
-    if (!a.do_norm) hipLaunchKernelGGL((post_norm_kernel<DT, CH, false, true, false>), g, b, lds, s, a);
-    else if (bias && gamma) hipLaunchKernelGGL((post_norm_kernel<DT, CH, true, true, true>), g, b, lds, s, a);
-    else if (bias) hipLaunchKernelGGL((post_norm_kernel<DT, CH, true, true, false>), g, b, lds, s, a);
-    else if (gamma) hipLaunchKernelGGL((post_norm_kernel<DT, CH, true, false, true>), g, b, lds, s, a);
-    else hipLaunchKernelGGL((post_norm_kernel<DT, CH, true, false, false>), g, b, lds, s, a);
+    if (!a.do_norm) hipLaunchKernelGGL((post_norm_kernel<DT, CH, WPR, FUSE, false, true, false>), g, b, lds, s, a);
+    else if (bias && gamma)
+        hipLaunchKernelGGL((post_norm_kernel<DT, CH, WPR, FUSE, true, true, true>), g, b, lds, s, a);
+    else if (bias) hipLaunchKernelGGL((post_norm_kernel<DT, CH, WPR, FUSE, true, true, false>), g, b, lds, s, a);
+    else if (gamma) hipLaunchKernelGGL((post_norm_kernel<DT, CH, WPR, FUSE, true, false, true>), g, b, lds, s, a);
+    else hipLaunchKernelGGL((post_norm_kernel<DT, CH, WPR, FUSE, true, false, false>), g, b, lds, s, a);
 }
 
-template <int DT>
-hipError_t launch_dt(const PostArgs& a, hipStream_t s) {
-    const int64_t nch = a.N >> 3;
-    const dim3 g((unsigned)((a.M + kRowsPerBlock - 1) / kRowsPerBlock)), b(kThreads);
-    if (!a.do_norm && !a.bias) hipLaunchKernelGGL((post_gather_kernel<DT>), g, b, post_lds_bytes(a), s, a);
-    else if (nch <= 64 * 4) launch_norm<DT, 4>(a, g, b, s);
-    else if (nch <= 64 * 8) launch_norm<DT, 8>(a, g, b, s);
-    else if (nch <= kMaxRegChunks) launch_norm<DT, 16>(a, g, b, s);
-    else launch_norm<DT, 0>(a, g, b, s);
-    return hipGetLastError();
+template <int DT, bool FUSE>
+void launch_form(const PostArgs& a, const PostForm& f, hipStream_t s) {
+    const dim3 g(f.blocks);
+    if (f.chunks < 0) {
+        if (f.waves_per_row == 1)
+            hipLaunchKernelGGL((post_gather_kernel<DT, 1, FUSE>), g, dim3(kThreads), f.lds, s, a);
+        else hipLaunchKernelGGL((post_gather_kernel<DT, 4, FUSE>), g, dim3(kThreads), f.lds, s, a);
+    } else if (f.waves_per_row == 4) {
+        if (f.chunks == 2) launch_norm<DT, 2, 4, FUSE>(a, g, f.lds, s);
+        else if (f.chunks == 4) launch_norm<DT, 4, 4, FUSE>(a, g, f.lds, s);
+        else launch_norm<DT, 8, 4, FUSE>(a, g, f.lds, s);
+    } else if (f.chunks == 4) {
+        launch_norm<DT, 4, 1, FUSE>(a, g, f.lds, s);
+    } else if (f.chunks == 8) {
+        launch_norm<DT, 8, 1, FUSE>(a, g, f.lds, s);
+    } else if (f.chunks == 16) {
+        launch_norm<DT, 16, 1, FUSE>(a, g, f.lds, s);
+    } else if constexpr (!FUSE) {
+        launch_norm<DT, 0, 1, false>(a, g, f.lds, s);
+    }
 }
 
 }  // namespace
 
-size_t post_lds_bytes(const PostArgs& a) {
+PostForm post_form(const PostArgs& a, bool fused) {
     const int64_t nch = a.N >> 3;
-    const bool norm_path = a.do_norm || a.bias;
-    const bool lds_affine = norm_path && (a.bias || (a.do_norm && a.gamma)) && nch <= kMaxRegChunks;
-    return (size_t)kRowsPerBlock * a.tiles_n * sizeof(uint32_t) + (lds_affine ? 2 * (size_t)nch * 16 : 0);
+    PostForm f{};
+    const bool norm = a.do_norm || a.bias;
+    const bool affine = norm && (a.bias || a.gamma);
+    // A workgroup per row where one wave could not hold the row in registers
+    // (us, one wave -> four: 1280x12288 bias + RMSNorm 25.3 -> 11.8), where the
+    // rows are too few to fill the device with waves (64x4096 fused 8.4 -> 5.9,
+    // 512x4096 8.9 -> 7.1; 640x2560 the other way, 5.7 -> 6.7), and for long rows
+    // (restore 8192x8192 52.7 -> 48.7, fused 103 -> 89; 4096x7168 with RMSNorm
+    // fused 37.5 -> 36.1, with bias 21.4 -> 19.7), unless many rows share bias
+    // and gamma, which four one-wave rows read from LDS (8192x8192 56.2 against
+    // 59.5). Shorter rows: one wave (2048x4096 6.5 -> 6.8, 8192x2048 11.9 -> 12.9).
+    const bool wide = nch > 64 * 16 || (a.M <= 512 && nch >= 256) ||
+                      ((affine || fused ? nch > 512 : nch >= 1024) && (!affine || a.M <= 4096));
+    f.waves_per_row = wide && (!norm || nch <= 256 * 8) ? 4 : 1;
+    if (!norm) f.chunks = -1;
+    else if (f.waves_per_row == 4) f.chunks = nch <= 256 * 2 ? 2 : nch <= 256 * 4 ? 4 : 8;
+    else f.chunks = nch <= 64 * 4 ? 4 : nch <= 64 * 8 ? 8 : nch <= 64 * 16 ? 16 : 0;
+    const int rows = kThreads / 64 / f.waves_per_row;
+    f.blocks = (uint32_t)((a.M + rows - 1) / rows);
+    const bool lds_affine = norm && (a.bias || a.gamma) && f.waves_per_row == 1 && f.chunks > 0;
+    f.lds = (size_t)rows * a.tiles_n * sizeof(uint32_t) * (fused ? 2 : 1) + (lds_affine ? 2 * (size_t)nch * 16 : 0);
+    return f;
 }
 
-hipError_t launch_post(int dtype, const PostArgs& a, hipStream_t s) {
+bool post_fusable(const PostArgs& a) {
+    const PostForm f = post_form(a, true);
+    return f.chunks != 0 && f.lds <= kMaxPostLds && a.M * a.N * 2 <= INT32_MAX && a.M * a.N > 0;
+}
+
+hipError_t launch_post(int dtype, const PostArgs& a, bool fused, hipStream_t s) {
     if (a.M == 0 || a.N == 0) return hipSuccess;
-    return dtype == FO_FP16 ? launch_dt<FO_FP16>(a, s) : launch_dt<FO_BF16>(a, s);
+    const PostForm f = post_form(a, fused);
+    if (dtype == FO_FP16) {
+        if (fused) launch_form<FO_FP16, true>(a, f, s);
+        else launch_form<FO_FP16, false>(a, f, s);
+    } else {
+        if (fused) launch_form<FO_BF16, true>(a, f, s);
+        else launch_form<FO_BF16, false>(a, f, s);
+    }
+    return hipGetLastError();
 }
 
 }  // namespace fo

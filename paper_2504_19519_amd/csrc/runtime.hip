@@ -203,6 +203,62 @@ fo_status consume_args(const uint16_t* src, const uint16_t* peer, uint16_t* dst,
     return FO_OK;
 }
 
+// Arguments of a post-reorder launch, checked (plan->M, plan->N > 0).
+fo_status post_args(const fo_plan* plan, const void* dev_plan, const void* src, void* out, const void* bias,
+                    const void* gamma, float eps, int32_t do_rmsnorm, PostArgs* post) {
+    if (!src || !out) return fail(FO_ERR_ARG, "null src or out");
+    if (!dev_plan && plan->pattern != FO_PATTERN_ROWMAJOR) return fail(FO_ERR_ARG, "dev_plan is NULL");
+    if (plan->N % 8 || plan->tile_n % 8) return fail(FO_ERR_UNSUPPORTED, "N and tile_n must be multiples of 8");
+    if (!aligned16(src) || !aligned16(out) || (bias && !aligned16(bias)) || (gamma && !aligned16(gamma)))
+        return fail(FO_ERR_ARG, "src, out, bias and gamma must be 16-byte aligned");
+    if (do_rmsnorm && !(eps >= 0.0f)) return fail(FO_ERR_ARG, "eps must be >= 0");
+    const fo_dev_layout& L = plan->layout;
+    PostArgs& a = *post;
+    a.src = static_cast<const uint16_t*>(src);
+    a.out = static_cast<uint16_t*>(out);
+    a.bias = static_cast<const uint16_t*>(bias);
+    a.gamma = static_cast<const uint16_t*>(gamma);
+    a.M = plan->M; a.N = plan->N;
+    a.tile_m = plan->tile_m; a.tile_n = plan->tile_n; a.tiles_n = plan->tiles_n;
+    {
+        const int cpt = plan->tile_n / 8;
+        a.cpt_log2 = -1;
+        for (int l = 0; l < 31; ++l)
+            if ((1 << l) == cpt) a.cpt_log2 = l;
+        if (plan->pattern != FO_PATTERN_ROWMAJOR && (plan->tile_n % 8 || a.cpt_log2 < 0))
+            return fail(FO_ERR_UNSUPPORTED, "post-reorder needs tile_n / 8 to be a power of two");
+        // row-major source: chunk c of a row lies at the row's first piece + c
+        if (plan->pattern == FO_PATTERN_ROWMAJOR) a.cpt_log2 = 31;
+    }
+    a.pattern = plan->pattern; a.num_dest = plan->num_dest;
+    a.per_dest = plan->pattern == FO_PATTERN_SUBTILE
+                     ? (int64_t)plan->tiles * (plan->tile_m / plan->num_dest) * plan->tile_n : 0;
+    if (dev_plan) {
+        a.tile_to_slot = dev_table<int32_t>(dev_plan, L.tile_to_slot);
+        a.slot_group = dev_table<int32_t>(dev_plan, L.slot_group);
+        a.group_first = dev_table<int32_t>(dev_plan, L.group_first);
+        a.dest_perm = dev_table<int32_t>(dev_plan, L.dest_perm);
+        a.row_bucket = dev_table<int32_t>(dev_plan, L.row_bucket);
+        a.row_rank = dev_table<int32_t>(dev_plan, L.row_rank);
+        a.pool_base = dev_table<int32_t>(dev_plan, L.pool_base);
+        a.pool_off = dev_table<int32_t>(dev_plan, L.pool_off);
+    }
+    a.eps = eps;
+    a.do_norm = do_rmsnorm ? 1 : 0;
+    // source pieces are addressed in 16-byte chunks with 32-bit offsets
+    if (std::max<int64_t>(plan->dest_elems, plan->M * plan->N) / 8 > (int64_t)UINT32_MAX)
+        return fail(FO_ERR_SHAPE, "post-reorder source buffer too large for 32-bit chunk offsets");
+    if (post_lds_bound(a) > kMaxPostLds)
+        return fail(FO_ERR_UNSUPPORTED, "post-reorder: too many tile columns or too wide a row for LDS");
+    return FO_OK;
+}
+
+// Whether [p, p + bytes) and [q, q + bytes) share a byte.
+bool overlap(const void* p, const void* q, int64_t bytes) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(p), y = reinterpret_cast<uintptr_t>(q);
+    return x < y ? y - x < (uintptr_t)bytes : x - y < (uintptr_t)bytes;
+}
+
 }  // namespace
 
 fo_status fail(fo_status st, const std::string& msg) {
@@ -389,53 +445,12 @@ fo_status fo_post_reorder(const fo_plan* plan, const void* dev_plan, const void*
     fo::clear_error();
     if (!plan) return fo::fail(FO_ERR_ARG, "plan is NULL");
     if (plan->M == 0 || plan->N == 0) return FO_OK;
-    if (!src || !out) return fo::fail(FO_ERR_ARG, "null src or out");
-    if (!dev_plan && plan->pattern != FO_PATTERN_ROWMAJOR) return fo::fail(FO_ERR_ARG, "dev_plan is NULL");
-    if (plan->N % 8 || plan->tile_n % 8) return fo::fail(FO_ERR_UNSUPPORTED, "N and tile_n must be multiples of 8");
-    if (!fo::aligned16(src) || !fo::aligned16(out) || (bias && !fo::aligned16(bias)) ||
-        (gamma && !fo::aligned16(gamma)))
-        return fo::fail(FO_ERR_ARG, "src, out, bias and gamma must be 16-byte aligned");
-    if (do_rmsnorm && !(eps >= 0.0f)) return fo::fail(FO_ERR_ARG, "eps must be >= 0");
-    const fo_dev_layout& L = plan->layout;
     fo::PostArgs a{};
-    a.src = static_cast<const uint16_t*>(src);
-    a.out = static_cast<uint16_t*>(out);
-    a.bias = static_cast<const uint16_t*>(bias);
-    a.gamma = static_cast<const uint16_t*>(gamma);
-    a.M = plan->M; a.N = plan->N;
-    a.tile_m = plan->tile_m; a.tile_n = plan->tile_n; a.tiles_n = plan->tiles_n;
-    {
-        const int cpt = plan->tile_n / 8;
-        a.cpt_log2 = -1;
-        for (int l = 0; l < 31; ++l)
-            if ((1 << l) == cpt) a.cpt_log2 = l;
-        if (plan->pattern != FO_PATTERN_ROWMAJOR && (plan->tile_n % 8 || a.cpt_log2 < 0))
-            return fo::fail(FO_ERR_UNSUPPORTED, "post-reorder needs tile_n / 8 to be a power of two");
-        // row-major source: chunk c of a row lies at the row's first piece + c
-        if (plan->pattern == FO_PATTERN_ROWMAJOR) a.cpt_log2 = 31;
-    }
-    a.pattern = plan->pattern; a.num_dest = plan->num_dest;
-    a.per_dest = plan->pattern == FO_PATTERN_SUBTILE
-                     ? (int64_t)plan->tiles * (plan->tile_m / plan->num_dest) * plan->tile_n : 0;
-    if (dev_plan) {
-        a.tile_to_slot = fo::dev_table<int32_t>(dev_plan, L.tile_to_slot);
-        a.dest_perm = fo::dev_table<int32_t>(dev_plan, L.dest_perm);
-        a.row_bucket = fo::dev_table<int32_t>(dev_plan, L.row_bucket);
-        a.row_rank = fo::dev_table<int32_t>(dev_plan, L.row_rank);
-        a.pool_base = fo::dev_table<int32_t>(dev_plan, L.pool_base);
-        a.pool_off = fo::dev_table<int32_t>(dev_plan, L.pool_off);
-    }
-    a.eps = eps;
-    a.do_norm = do_rmsnorm ? 1 : 0;
-    // source pieces are addressed in 16-byte chunks with 32-bit offsets
-    if (std::max<int64_t>(plan->dest_elems, plan->M * plan->N) / 8 > (int64_t)UINT32_MAX)
-        return fo::fail(FO_ERR_SHAPE, "post-reorder source buffer too large for 32-bit chunk offsets");
-    if (fo::post_lds_bytes(a) > 64 * 1024)
-        return fo::fail(FO_ERR_UNSUPPORTED, "post-reorder: too many tile columns or too wide a row for LDS");
-    hipError_t e = fo::launch_post(plan->dtype, a, (hipStream_t)stream);
+    const fo_status st = fo::post_args(plan, dev_plan, src, out, bias, gamma, eps, do_rmsnorm, &a);
+    if (st != FO_OK) return st;
+    hipError_t e = fo::launch_post(plan->dtype, a, false, (hipStream_t)stream);
     return e == hipSuccess ? FO_OK : fo::hip_fail("post-reorder launch", e);
 }
-
 
 fo_status fo_run_overlapped(const fo_plan* plan, const void* dev_plan, const void* A, const void* W,
                             void* C_out, const void* peer, void* dst, void* out, const void* bias,
@@ -486,6 +501,29 @@ fo_status fo_run_overlapped(const fo_plan* plan, const void* dev_plan, const voi
         return st;
     if (gemm_end_event && (e = hipEventRecord((hipEvent_t)gemm_end_event, s1)) != hipSuccess)
         return fo::hip_fail("hipEventRecord", e);
+    // A run on one stream: the consumer is fused into the post-reorder (one
+    // pass over the GEMM's output and the peer's partial that writes dst and
+    // out, without a launch of its own and a second read of dst; us for both
+    // kernels, then fused: 16384x4096 bf16 with bias and RMSNorm 114 -> 89,
+    // 8192x8192 113 -> 101, 1216x2880 14.7 -> 9.8). Not where the consumers are
+    // capped (every group then goes over the emulated link), where out lies on
+    // a buffer that the consumer reads, or where the peer's alignment or the
+    // sizes keep the fused form from its 16-byte accesses.
+    fo::PostArgs post{};
+    bool fused = !overlap && out && o.consumer_limit == 0 && plan->M > 0 && plan->N > 0 && fo::aligned16(peer);
+    if (fused) {
+        const int64_t bytes = plan->M * plan->N * 2;
+        fused = fo::post_args(plan, dev_plan, dst, out, bias, gamma, eps, do_rmsnorm, &post) == FO_OK &&
+                fo::post_fusable(post) && !fo::overlap(out, C_out, bytes) &&
+                !(peer && fo::overlap(out, peer, bytes));
+    }
+    if (fused) {
+        post.gemm_out = static_cast<const uint16_t*>(C_out);
+        post.peer = static_cast<const uint16_t*>(peer);
+        post.bytes = (uint32_t)(plan->M * plan->N * 2);
+        e = fo::launch_post(plan->dtype, post, true, s1);
+        return e == hipSuccess ? FO_OK : fo::hip_fail("post-reorder launch", e);
+    }
     // One consumer launch per group (more if a group has more pieces than a
     // launch carries), as a collective library would take one call per
     // group. Groups before the last one share the device with the GEMM and
