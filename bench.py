@@ -333,7 +333,12 @@ def consumer_curve(torch, w, b, stream, total_elems, beside=None):
         if n == total_elems:
             break
         n = min(n * 2, total_elems)
-    launch = lambda n: fo.consume_group(b.C, b.peer, b.dst, n, w.dtype, None, 0, None, stream, opts=OPTS)
+    # (a cap of 256 workgroups, the whole grid, gives the kernel that a group
+    # gets beside the GEMM in an overlapped run)
+    opts = fo.options() if OPTS is None else fo.Options.from_buffer_copy(OPTS)
+    if opts.consumer_limit == 0:
+        opts.consumer_limit = 256
+    launch = lambda n: fo.consume_group(b.C, b.peer, b.dst, n, w.dtype, None, 0, None, stream, opts=opts)
     if beside is None:
         return [2.0 * n for n in sizes], [time_loop(torch, lambda: launch(n), 20, 3, stream) for n in sizes]
     plan, dp = beside

@@ -354,7 +354,10 @@ fo_status fo_gemm_signal_reorder(const fo_plan* plan, const void* dev_plan,
  * (options->poll_timeout_us); on timeout the segment is not written and
  * *status_word (if non-NULL, device uint32) gets bit 0 set; the library
  * never clears it. The launch uses options->consumer_blocks and
- * consumer_threads (capped by consumer_limit) and the consumer sync mode.
+ * consumer_threads (capped by consumer_limit) and the consumer sync mode; with
+ * one-wave workgroups and no cap it streams through 24 KB of LDS per workgroup,
+ * faster than a group's launch inside fo_run_overlapped (which a cap of 256
+ * gives here too).
  * Buffers must not overlap. Any alignment works; 16-byte-aligned pointers
  * take the vector path.
  * Errors: FO_ERR_ARG (null src/dst with len > 0, len < 0, bad dtype, an

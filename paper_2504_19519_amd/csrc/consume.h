@@ -37,9 +37,11 @@ struct ConsumeArgs {
 // max_blocks caps the grid (1 .. kMaxConsumeBlocks); threads per workgroup:
 // 64, 128 or 256. full: the launch has the device to itself (more accesses
 // in flight per thread); otherwise it runs beside the GEMM and keeps its
-// registers within what a SIMD running two GEMM waves has left.
+// registers within what a SIMD running two GEMM waves has left. ring: a launch
+// of one-wave workgroups may stream through LDS (coherent mode, 16-byte aligned
+// buffers).
 // *blocks (if non-null) receives the streaming kernel's grid size.
-hipError_t launch_consume(int dtype, int sync, const ConsumeArgs& a, int max_blocks, int threads, bool full,
+hipError_t launch_consume(int dtype, int sync, const ConsumeArgs& a, int max_blocks, int threads, bool full, bool ring,
                           hipStream_t s, int* blocks = nullptr);
 
 // One wave that polls until *counter >= target (bounded by timeout_ticks;

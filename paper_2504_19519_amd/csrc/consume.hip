@@ -17,10 +17,10 @@
 // workgroups write nothing and bit 0 of the status word is raised, so a
 // missing signal can never hang the device.
 //
-// A consumer workgroup holds 4 bytes of LDS and at most 56 registers per
-// lane, so it fits beside a GEMM workgroup on the same compute unit (the
-// GEMM kernels leave at least 64 registers per SIMD lane and 10 KB of LDS
-// free): polling consumers share compute units with the GEMM instead of
+// A consumer workgroup holds 4 bytes of LDS (24 KB with a ring) and at most 57
+// registers per lane, so it fits beside a GEMM workgroup on the same compute
+// unit (the GEMM kernels leave at least 64 registers per SIMD lane and 26 KB of
+// LDS free): polling consumers share compute units with the GEMM instead of
 // taking them away from it.
 #include <hip/hip_runtime.h>
 
@@ -42,6 +42,9 @@ constexpr int kUnrollFull = 4;
 constexpr int kUnrollBeside = 2;
 // s_waitcnt operand: vmcnt(0), other counters not waited for
 constexpr int kWaitVmcnt0 = 0x0F70;
+
+// the same for vmcnt(n)
+constexpr int wait_vm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
 
 // Destination stores. Nontemporal by default (the next kernel reads the data,
 // not this one). WT: device-coherent write-through stores (sc1), used by the
@@ -313,6 +316,132 @@ __device__ __forceinline__ void stream_coherent16(const uint16_t* __restrict__ s
     }
 }
 
+// All segments of a launch of one-wave workgroups, through a ring in LDS
+// (COHERENT; 16-byte aligned buffers of any size). Such a launch has one wave
+// per compute unit, so what it streams is what that wave keeps in flight over a
+// memory latency; the registers that a GEMM wave leaves it hold 4 KB, the LDS
+// beside a GEMM workgroup 24 KB. Direct-to-LDS loads (sc1 and nontemporal, as
+// in stream_coherent16) run D batches of 128 chunks ahead; the wave waits for
+// the oldest batch only, adds the peer's, stores, and loads the batch D further
+// on in its place. A batch past the wave's last one is loaded through an empty
+// resource, so that every round has the same number of operations in flight.
+// Alone, 256 workgroups (us, register path -> ring; floor at 5.1 TB/s): sum of
+// 8388613 fp16 23.7 -> 12.5 (9.9) with its wait kernel, copy of 29360128 38.9 ->
+// 26.3 (23.0); rings of 8 and 16 KB: 16.7 and 13.2, 27.6 and 26.0. Beside the
+// GEMM it takes more from the GEMM than it gains (overlapped runs with rings of
+// 8 / 24 KB: 8192x8192x3584 461 -> 465 / 468, 16384x4096x3584 447 -> 447 / 449),
+// so the groups of an overlapped run keep the register path.
+template <int DT, bool SUM, bool WT>
+__device__ __forceinline__ void stream_ring(const ConsumeArgs& a) {
+    constexpr int kRing = 24 * 1024, kBatch = 2048, kSlot = SUM ? 2 * kBatch : kBatch, D = kRing / kSlot;
+    constexpr int kLoads = kSlot / 1024, kOps = kLoads + 2;     // per round: the loads, two stores
+    static_assert((D - 1) * kOps <= 63, "the rounds in flight fit the vector memory counter");
+    constexpr int kSc1Nt = 16 | 2;   // cache policy operand: sc1, nt
+    __shared__ __attribute__((aligned(1024))) char ring[kRing];
+    typedef __attribute__((address_space(3))) char lds_char_t;
+    typedef __attribute__((address_space(3))) void lds_void_t;
+    const int lane = threadIdx.x;
+    const int64_t grid = gridDim.x;
+    // This wave's batches: every grid-th of the segments' batches in a row. A
+    // cursor holds its segment's bounds in scalar registers; the segment table
+    // is only read again when a segment ends.
+    struct Cursor {
+        int k;
+        int64_t u, n;              // batch u of the segment's n
+        int64_t from, to, bytes;   // byte offsets of the segment, its whole chunks
+    };
+    auto enter = [&](Cursor& c) {
+        while (c.k < a.nseg) {
+            const ConsumeSegment g = a.seg[c.k];
+            c.from = g.src_off * 2;
+            c.to = g.dst_off * 2;
+            c.bytes = (g.len >> 3) * 16;
+            c.n = (c.bytes + kBatch - 1) / kBatch;
+            if (c.u < c.n) return;
+            c.u -= c.n;
+            ++c.k;
+        }
+        c.u = c.bytes = c.from = 0;    // past the last one: nothing to load
+    };
+    auto next = [&](Cursor& c) {
+        c.u += grid;
+        if (c.u >= c.n && c.k < a.nseg) {
+            c.u -= c.n;
+            ++c.k;
+            enter(c);
+        }
+    };
+    auto load = [&](const Cursor& c, int slot) {
+        const int64_t at = c.u * kBatch, left = c.bytes - at;
+        const int bytes = c.k >= a.nseg ? 0 : (int)(left < kBatch ? left : kBatch);
+        char* const to = ring + slot * kSlot;
+#pragma unroll
+        for (int x = 0; x < kLoads / 2; ++x) {
+            const char* from = reinterpret_cast<const char*>(x == 0 ? a.src : a.peer) + c.from + at;
+            const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)from, 0, bytes, kRsrcWord3);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)(to + x * kBatch), 16, lane * 16, 0, 0, kSc1Nt);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)(to + x * kBatch + 1024), 16, lane * 16 + 1024, 0,
+                                                     0, kSc1Nt);
+        }
+    };
+    Cursor ahead{0, (int64_t)blockIdx.x, 0, 0, 0, 0};
+    enter(ahead);
+    Cursor now = ahead;
+    for (int d = 0; d < D; ++d) {
+        load(ahead, d);
+        next(ahead);
+    }
+    const uint32_t base = (uint32_t)(uintptr_t)(lds_char_t*)ring + (uint32_t)lane * 16u;
+    int slot = 0;
+    for (int round = 0; now.k < a.nseg; ++round) {
+        // the loads of this slot are the oldest ones: younger are the loads of
+        // D - 1 rounds and, once the first D rounds are over, their stores
+        asm volatile("" ::: "memory");
+        if (round < D) __builtin_amdgcn_s_waitcnt(wait_vm((D - 1) * kLoads));
+        else __builtin_amdgcn_s_waitcnt(wait_vm((D - 1) * kOps));
+        const uint32_t at = base + (uint32_t)(slot * kSlot);
+        u32x4_t x0, x1;
+        // (read in assembly: for a plain LDS read the compiler would wait for
+        // every direct-to-LDS load in flight)
+        if constexpr (SUM) {
+            u32x4_t y0, y1;
+            asm volatile("ds_read_b128 %0, %4\n ds_read_b128 %1, %4 offset:1024\n ds_read_b128 %2, %4 offset:2048\n"
+                         " ds_read_b128 %3, %4 offset:3072\n s_waitcnt lgkmcnt(0)"
+                         : "=&v"(x0), "=&v"(x1), "=&v"(y0), "=&v"(y1) : "v"(at) : "memory");
+            x0 = add8<DT>(x0, y0);
+            x1 = add8<DT>(x1, y1);
+        } else {
+            asm volatile("ds_read_b128 %0, %2\n ds_read_b128 %1, %2 offset:1024\n s_waitcnt lgkmcnt(0)"
+                         : "=&v"(x0), "=&v"(x1) : "v"(at) : "memory");
+        }
+        // (through a resource that ends with the segment, not under a branch:
+        // both stores are issued in every round, as the wait above counts them)
+        const int64_t left = now.bytes - now.u * kBatch;
+        const __amdgpu_buffer_rsrc_t d =
+            __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char*>(a.dst) + now.to + now.u * kBatch, 0,
+                                              (int)(left < kBatch ? left : kBatch), kRsrcWord3);
+        __builtin_amdgcn_raw_buffer_store_b128(x0, d, lane * 16, 0, WT ? 16 : 2);    // sc1 (see put16), or nt
+        __builtin_amdgcn_raw_buffer_store_b128(x1, d, lane * 16 + 1024, 0, WT ? 16 : 2);
+        asm volatile("" ::: "memory");
+        load(ahead, slot);
+        next(ahead);
+        next(now);
+        slot = slot + 1 == D ? 0 : slot + 1;
+    }
+    // ragged tails (< 8 elements): an acquire, then plain 2-byte loads
+    if (blockIdx.x == 0) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        for (int k = 0; k < a.nseg; ++k) {
+            const ConsumeSegment g = a.seg[k];
+            if (lane >= (g.len & 7)) continue;
+            const int64_t e = (g.len >> 3 << 3) + lane;
+            const uint16_t x = a.src[g.src_off + e];
+            put2<WT>(a.dst + g.dst_off + e, SUM ? add1<DT>(x, a.peer[g.src_off + e]) : x);
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);    // no load may still be writing LDS
+}
+
 // Stream one segment element by element (unaligned buffers).
 template <int DT, bool SUM, bool WT>
 __device__ __forceinline__ void stream_elem(const uint16_t* __restrict__ src, const uint16_t* __restrict__ peer,
@@ -324,7 +453,7 @@ __device__ __forceinline__ void stream_elem(const uint16_t* __restrict__ src, co
     i0 = (uint32_t)(i - len);
 }
 
-enum { kPathVec16 = 0, kPathCoherent8 = 1, kPathElem = 2, kPathCoherent16 = 3 };
+enum { kPathVec16 = 0, kPathCoherent8 = 1, kPathElem = 2, kPathCoherent16 = 3, kPathRing = 4 };
 
 // SYNC: how the group is published to the workgroup (check_counter).
 // PATH: kPathCoherent16 / kPathCoherent8 go with SYNC == COHERENT;
@@ -336,7 +465,10 @@ enum { kPathVec16 = 0, kPathCoherent8 = 1, kPathElem = 2, kPathCoherent16 = 3 };
 // another stream covers the whole launch.
 template <int DT, bool SUM, int SYNC, int PATH, int U, bool WT>
 __global__ __launch_bounds__(kMaxThreads) void consume_kernel(const ConsumeArgs a) {
-    if (!a.counter || check_counter<SYNC>(a.counter, a.target, a.status)) {
+    const bool go = !a.counter || check_counter<SYNC>(a.counter, a.target, a.status);
+    if constexpr (PATH == kPathRing) {
+        if (go) stream_ring<DT, SUM, WT>(a);
+    } else if (go) {
         uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;   // < grid size: fits 32 bits
         for (int k = 0; k < a.nseg; ++k) {
             const ConsumeSegment g = a.seg[k];
@@ -365,7 +497,9 @@ constexpr int kUnit8Unroll = DT == FO_BF16 ? (U < 2 ? U : 2) : (U < 4 ? U : 4);
 
 template <int DT, bool SUM, int U, bool WT>
 void launch_variant(int sync, int path, dim3 g, dim3 b, hipStream_t s, const ConsumeArgs& a) {
-    if (path == kPathCoherent16)
+    if (path == kPathRing)
+        hipLaunchKernelGGL((consume_kernel<DT, SUM, FO_SYNC_COHERENT, kPathRing, 1, WT>), g, b, 0, s, a);
+    else if (path == kPathCoherent16)
         hipLaunchKernelGGL((consume_kernel<DT, SUM, FO_SYNC_COHERENT, kPathCoherent16, U, WT>), g, b, 0, s, a);
     else if (path == kPathCoherent8)   // bf16 sums: fewer 8-byte units in flight (the budget of registers)
         hipLaunchKernelGGL((consume_kernel<DT, SUM, FO_SYNC_COHERENT, kPathCoherent8, kUnit8Unroll<DT, U>, WT>), g,
@@ -411,7 +545,7 @@ hipError_t launch_gate(uint32_t* gate, uint32_t tag, uint32_t* status, uint64_t 
     return hipGetLastError();
 }
 
-hipError_t launch_consume(int dtype, int sync, const ConsumeArgs& a, int max_blocks, int threads, bool full,
+hipError_t launch_consume(int dtype, int sync, const ConsumeArgs& a, int max_blocks, int threads, bool full, bool ring,
                           hipStream_t s, int* launched_blocks) {
     // The path is chosen once for the launch: every segment's pointers must
     // allow it.
@@ -428,14 +562,16 @@ hipError_t launch_consume(int dtype, int sync, const ConsumeArgs& a, int max_blo
     // the 16-byte coherent path addresses a segment with 32-bit byte offsets
     const bool fits32 = longest * 2 <= 0x7FFFFFFF;
     const int path = sync == FO_SYNC_COHERENT
-                         ? (vec16 && fits32 ? kPathCoherent16 : vec8 ? kPathCoherent8 : kPathElem)
+                         ? (vec16 && threads == 64 && ring ? kPathRing
+                            : vec16 && fits32 ? kPathCoherent16 : vec8 ? kPathCoherent8 : kPathElem)
                          : (vec16 ? kPathVec16 : kPathElem);
     // elements one workgroup moves per unrolled round (the unrolls of
     // launch_unroll and kUnit8Unroll), for the grid of a short launch
     const bool sum = a.peer != nullptr;
     const int unroll = (full ? kUnrollFull : kUnrollBeside) * (sum ? 1 : 2);
     const int unroll8 = dtype == FO_BF16 ? (unroll < 2 ? unroll : 2) : (unroll < 4 ? unroll : 4);
-    const int64_t per_block = path == kPathCoherent8 ? (int64_t)threads * 2 * unroll8 * 4
+    const int64_t per_block = path == kPathRing ? 1024
+                              : path == kPathCoherent8 ? (int64_t)threads * 2 * unroll8 * 4
                               : path == kPathVec16 || path == kPathCoherent16 ? (int64_t)threads * unroll * 8
                                                                                : (int64_t)threads;
     int64_t blocks = (total + per_block - 1) / per_block;

@@ -435,7 +435,7 @@ fo_status fo_consume_group(const void* src, const void* peer, void* dst, int64_t
     a.nseg = 1;
     a.seg[0] = fo::ConsumeSegment{0, 0, len};
     hipError_t e = fo::launch_consume(dtype, o.sync_consumer, a, fo::limited(o, o.consumer_blocks),
-                                      o.consumer_threads, false, (hipStream_t)stream);
+                                      o.consumer_threads, false, o.consumer_limit == 0, (hipStream_t)stream);
     return e == hipSuccess ? FO_OK : fo::hip_fail("consumer launch", e);
 }
 
@@ -565,7 +565,7 @@ fo_status fo_run_overlapped(const fo_plan* plan, const void* dev_plan, const voi
         const bool last = launches[k].last;
         const int blocks = fo::limited(o, last ? fo::kMaxConsumeBlocks : cap);
         const int threads = last ? 256 : cap_threads;
-        if ((e = fo::launch_consume(plan->dtype, sync, c, blocks, threads, last && !capped, overlap ? s2 : s1,
+        if ((e = fo::launch_consume(plan->dtype, sync, c, blocks, threads, last && !capped, false, overlap ? s2 : s1,
                                     final_launch ? &final_blocks : nullptr)) != hipSuccess)
             return fo::hip_fail("consumer launch", e);
     }
