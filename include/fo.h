@@ -398,6 +398,14 @@ fo_status fo_reset_counters(uint32_t* counters, int32_t n, void* stream);
  *   gemm_stream: reset kernel -> GEMM (signalling) -> done wait
  *                -> fo_post_reorder (if out != NULL)
  *   comm_stream: gate kernel -> one consumer launch per group
+ * A short run with an out (GEMM below 300 us, or below three times the time of
+ * its consumer, both estimated from the sizes and W) whose options leave the
+ * consumer grid and the sync modes at their built-in defaults consumes all
+ * groups in one launch behind the GEMM, fused with the post-reorder (the same
+ * values in dst and out, the counters as below):
+ *   gemm_stream: reset kernel -> GEMM (signalling) -> done wait
+ *   comm_stream: gate and wait for every counter -> consumer + post-reorder
+ *                [-> mark kernel, when its workgroups are too many to be counted]
  * The two streams hand work to each other on the device, not with events:
  * the reset kernel zeroes counters[0, P + FO_DISPENSER_WORDS), writes the
  * run's tag (a process-wide sequence number) into the 8 done words

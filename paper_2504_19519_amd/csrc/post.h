@@ -29,6 +29,8 @@ struct PostArgs {
     const uint16_t* gemm_out;
     const uint16_t* peer;
     uint32_t bytes;
+    uint32_t* done;             // counts finished workgroups (see ConsumeArgs), or null
+    uint32_t done_tag;
     const int32_t* slot_group;
     const int32_t* group_first;
 };

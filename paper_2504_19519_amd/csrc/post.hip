@@ -33,6 +33,7 @@
 // nontemporal.
 #include <hip/hip_runtime.h>
 
+#include "consume.h"
 #include "fo_device.h"
 #include "fo_internal.h"
 #include "post.h"
@@ -43,6 +44,7 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kRsrcWord3 = 0x00020000;      // raw byte-addressed buffer accesses
 constexpr int kSc1Nt = 16 | 2;              // cache policy: device-coherent and nontemporal
+constexpr int kWaitVmcnt0 = 0x0F70;         // s_waitcnt operand: vmcnt(0), other counters not waited for
 
 typedef __attribute__((address_space(3))) char lds_char_t;
 typedef __attribute__((address_space(3))) uint32_t lds_u32_t;
@@ -142,7 +144,7 @@ __device__ __forceinline__ void load_chunks(const PostArgs& a, const Pieces<FUSE
         const __amdgpu_buffer_rsrc_t rc =
             __builtin_amdgcn_make_buffer_rsrc((void*)a.gemm_out, 0, (int)a.bytes, kRsrcWord3);
         const u32x4_t* q = reinterpret_cast<const u32x4_t*>(a.peer);
-        u32x4_t* d = const_cast<u32x4_t*>(reinterpret_cast<const u32x4_t*>(a.src));
+        const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc((void*)a.src, 0, (int)a.bytes, kRsrcWord3);
         constexpr int S = B < 8 ? B : 8;            // chunks in flight at once
 #pragma unroll
         for (int b = 0; b < B; b += S) {
@@ -159,9 +161,34 @@ __device__ __forceinline__ void load_chunks(const PostArgs& a, const Pieces<FUSE
 #pragma unroll
             for (int t = 0; t < S; ++t) {
                 if (q) v[b + t] = add8<DT>(v[b + t], y[t]);
-                if (c0 + step * (b + t) < nch) __builtin_nontemporal_store(v[b + t], d + to[t]);
+                if (c0 + step * (b + t) < nch)
+                    __builtin_amdgcn_raw_buffer_store_b128(v[b + t], rd, (int)(to[t] * 16u), 0, kSc1Nt);
             }
         }
+    }
+}
+
+// Chunk c of the output row that starts at chunk `row`. The fused form writes
+// device-coherent (at the same rate), so that its workgroups can be counted.
+template <bool FUSE>
+__device__ __forceinline__ void put_out(const PostArgs& a, u32x4_t* out4, int64_t row, int c, u32x4_t v) {
+    if constexpr (FUSE) {
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)a.out, 0, (int)a.bytes, kRsrcWord3);
+        __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)((uint32_t)(row + c) * 16u), 0, kSc1Nt);
+    } else {
+        __builtin_nontemporal_store(v, out4 + c);
+    }
+}
+
+// End of a fused launch's workgroup that is counted (as the consumer's final
+// launch counts its own): its write-through stores are complete.
+template <bool FUSE>
+__device__ __forceinline__ void finished(const PostArgs& a) {
+    if constexpr (FUSE) {
+        if (!a.done) return;
+        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+        __syncthreads();
+        if (threadIdx.x == 0) count_done(a.done, a.done_tag);
     }
 }
 
@@ -192,9 +219,10 @@ __global__ __launch_bounds__(kThreads) void post_gather_kernel(const PostArgs a)
             }
 #pragma unroll
             for (int t = 0; t < B; ++t)
-                if (c0 + kLanes * t < nch) __builtin_nontemporal_store(v[t], out4 + c0 + kLanes * t);
+                if (c0 + kLanes * t < nch) put_out<FUSE>(a, out4, i * nch, c0 + kLanes * t, v[t]);
         }
     }
+    finished<FUSE>(a);
 }
 
 // y = (x + bias) [* rsqrt(mean((x + bias)^2) + eps) * gamma]. NORM, BIAS and
@@ -316,10 +344,11 @@ __global__ __launch_bounds__(kThreads) void post_norm_kernel(const PostArgs a) {
             for (int t = 0; t < CH; ++t) {
                 const int c = ln + kLanes * t;
                 const u32x4_t o = finish(c < nch ? c : nch - 1, xc[t], inv, sb, sg);
-                if (c < nch) __builtin_nontemporal_store(o, out4 + c);
+                if (c < nch) put_out<FUSE>(a, out4, i * nch, c, o);
                 if constexpr (kLdsAffine) asm volatile("" ::: "memory");
             }
         }
+        finished<FUSE>(a);
     } else {
         if (i >= a.M) return;
         auto at = [&](int c) { return reinterpret_cast<const u32x4_t*>(a.src)[pieces.chunk(a, w, c)[0]]; };

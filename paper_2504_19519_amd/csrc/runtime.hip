@@ -253,6 +253,33 @@ fo_status post_args(const fo_plan* plan, const void* dev_plan, const void* src, 
     return FO_OK;
 }
 
+// Whether the options leave the consumer launches of an overlapped run as they
+// are built (a caller that sets their grid or a sync mode gets one per group).
+bool plain_consumer(const fo_options& o) {
+    return o.consumer_blocks == kMaxConsumeBlocks && o.consumer_threads == 64 && o.consumer_limit == 0 &&
+           o.sync_producer == FO_SYNC_COHERENT && o.sync_consumer == FO_SYNC_COHERENT;
+}
+
+// Whether the groups of an overlapped run are consumed together, after the
+// GEMM. On one device a consumer beside the GEMM takes from the GEMM about what
+// it saves behind it, and every group costs a wait kernel and a launch, while
+// consumed together the groups share one pass with the post-reorder. Measured
+// (us per run, a launch per group / together):
+//   256x256x256    4 groups   49 / 20      4096x7168x2048   2 groups  148 / 130
+//   1216x2880x1984 4 groups   60 / 33      8192x4096x4096   2 groups  254 / 250
+//   4096x4096x4096 2 groups  170 / 146     8192x8192x1024   3 groups  290 / 213
+//   16384x8192x2048 4 groups 610 / 598     8192x8192x3584   3 groups  459 / 451
+//   16384x4096x3584 4 groups 446 / 446     32768x4096x3584  4 groups  877 / 889
+//   8192x8192x7168 4 groups  755 / 768
+// A launch per group pays once the GEMM (at the 5.5 TFLOP/s that a compute unit
+// reaches) lasts 300 us and three times as long as the consumer alone (at 5.1
+// TB/s): below that the groups after the first still run when the GEMM ends.
+bool short_run(const fo_plan& p, bool sum) {
+    const double gemm_us = 2.0 * (double)p.M * (double)p.N * (double)p.K / (std::max(p.W, 1) * 5.5e6);
+    const double consume_us = 2.0 * (double)p.M * (double)p.N * (sum ? 3 : 2) / 5.1e6;
+    return gemm_us < 300.0 || gemm_us < 3.0 * consume_us;
+}
+
 // Whether [p, p + bytes) and [q, q + bytes) share a byte.
 bool overlap(const void* p, const void* q, int64_t bytes) {
     const uintptr_t x = reinterpret_cast<uintptr_t>(p), y = reinterpret_cast<uintptr_t>(q);
@@ -487,12 +514,34 @@ fo_status fo_run_overlapped(const fo_plan* plan, const void* dev_plan, const voi
     const uint32_t seq = fo::g_run_seq.fetch_add(1, std::memory_order_relaxed);
     const uint32_t tag = fo::kGateTag | (seq & fo::kGateSeqMask);
     const uint32_t done_tag = fo::done_tag_of(seq);
+    // The consumer fused into the post-reorder: one pass over the GEMM's output
+    // and the peer's partial that writes dst and out, without a launch of its
+    // own and a second read of dst (us for both kernels, then fused:
+    // 16384x4096 bf16 with bias and RMSNorm 114 -> 89, 8192x8192 113 -> 89,
+    // 1216x2880 14.7 -> 9.4). For runs on one stream, and for short overlapped
+    // runs, whose groups are consumed together behind the GEMM. Not where
+    // the consumers are capped (every group then goes over the emulated link),
+    // where out lies on a buffer that the consumer reads, or where the peer's
+    // alignment or the sizes keep the fused form from its 16-byte accesses.
+    fo::PostArgs post{};
+    const int64_t bytes = plan->M * plan->N * 2;
+    bool fused = out && C_out && o.consumer_limit == 0 && bytes > 0 && fo::aligned16(peer) &&
+                 (!overlap || (dev_plan && fo::plain_consumer(o) && fo::short_run(*plan, peer != nullptr)));
+    if (fused)
+        fused = fo::post_args(plan, dev_plan, dst, out, bias, gamma, eps, do_rmsnorm, &post) == FO_OK &&
+                fo::post_fusable(post) && !fo::overlap(out, C_out, bytes) &&
+                !(peer && fo::overlap(out, peer, bytes));
+    if (fused) {
+        post.gemm_out = static_cast<const uint16_t*>(C_out);
+        post.peer = static_cast<const uint16_t*>(peer);
+        post.bytes = (uint32_t)bytes;
+    }
     if (overlap) {
         hipLaunchKernelGGL(fo::reset_run_kernel, dim3(1), dim3(256), 0, s1, counters, plan->P + FO_DISPENSER_WORDS,
                            done, done_tag, status_word, gate, tag);
         if ((e = hipGetLastError()) != hipSuccess) return fo::hip_fail("reset kernel launch", e);
     }
-    if (overlap && (e = fo::launch_gate(gate, tag, status_word, ticks, s2)) != hipSuccess)
+    if (overlap && !fused && (e = fo::launch_gate(gate, tag, status_word, ticks, s2)) != hipSuccess)
         return fo::hip_fail("gate kernel launch", e);
     if (gemm_begin_event && (e = hipEventRecord((hipEvent_t)gemm_begin_event, s1)) != hipSuccess)
         return fo::hip_fail("hipEventRecord", e);
@@ -501,28 +550,30 @@ fo_status fo_run_overlapped(const fo_plan* plan, const void* dev_plan, const voi
         return st;
     if (gemm_end_event && (e = hipEventRecord((hipEvent_t)gemm_end_event, s1)) != hipSuccess)
         return fo::hip_fail("hipEventRecord", e);
-    // A run on one stream: the consumer is fused into the post-reorder (one
-    // pass over the GEMM's output and the peer's partial that writes dst and
-    // out, without a launch of its own and a second read of dst; us for both
-    // kernels, then fused: 16384x4096 bf16 with bias and RMSNorm 114 -> 89,
-    // 8192x8192 113 -> 101, 1216x2880 14.7 -> 9.8). Not where the consumers are
-    // capped (every group then goes over the emulated link), where out lies on
-    // a buffer that the consumer reads, or where the peer's alignment or the
-    // sizes keep the fused form from its 16-byte accesses.
-    fo::PostArgs post{};
-    bool fused = !overlap && out && o.consumer_limit == 0 && plan->M > 0 && plan->N > 0 && fo::aligned16(peer);
-    if (fused) {
-        const int64_t bytes = plan->M * plan->N * 2;
-        fused = fo::post_args(plan, dev_plan, dst, out, bias, gamma, eps, do_rmsnorm, &post) == FO_OK &&
-                fo::post_fusable(post) && !fo::overlap(out, C_out, bytes) &&
-                !(peer && fo::overlap(out, peer, bytes));
-    }
-    if (fused) {
-        post.gemm_out = static_cast<const uint16_t*>(C_out);
-        post.peer = static_cast<const uint16_t*>(peer);
-        post.bytes = (uint32_t)(plan->M * plan->N * 2);
+    if (fused && !overlap) {
         e = fo::launch_post(plan->dtype, post, true, s1);
         return e == hipSuccess ? FO_OK : fo::hip_fail("post-reorder launch", e);
+    }
+    if (fused) {
+        // one wait for all counters (behind the GEMM launch, which may have been
+        // refused) and one launch for all groups, counted by its own workgroups or, when they
+        // are many (about 60 ns each for the read and the add on one of the done
+        // words), by a kernel of one thread behind it
+        if ((e = fo::launch_gate_all(gate, tag, counters, post.group_first, plan->P, status_word, ticks, s2)) !=
+            hipSuccess)
+            return fo::hip_fail("gate kernel launch", e);
+        const bool mark = fo::post_form(post, true).blocks > 512;
+        if (!mark) {
+            post.done = done;
+            post.done_tag = done_tag;
+        }
+        if ((e = fo::launch_post(plan->dtype, post, true, s2)) != hipSuccess)
+            return fo::hip_fail("post-reorder launch", e);
+        if (mark && (e = fo::launch_mark_done(done, done_tag, s2)) != hipSuccess)
+            return fo::hip_fail("mark kernel launch", e);
+        const int blocks = mark ? 1 : (int)fo::post_form(post, true).blocks;
+        e = fo::launch_done_wait(done, done_tag, blocks, status_word, ticks, s1);
+        return e == hipSuccess ? FO_OK : fo::hip_fail("wait kernel launch", e);
     }
     // One consumer launch per group (more if a group has more pieces than a
     // launch carries), as a collective library would take one call per
