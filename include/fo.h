@@ -327,8 +327,9 @@ fo_status fo_options_init(fo_options* o);
  * against W; up to 2 W workgroups run at a time when no compute units are
  * reserved, blocks take the plan's dispatch order with bands of the same
  * height, and a block's tiles of one group are counted by one add. With a
- * block per workgroup the position words stay untouched. Results do not depend
- * on the block.
+ * block per workgroup the position words stay untouched. Without counters the
+ * larger tiles too are computed in 128x128 blocks where that fills the last wave
+ * better. Results do not depend on the block.
  * dev_plan: the plan's device image (fo_plan_to_device).
  * Errors: FO_ERR_ARG, FO_ERR_SHAPE (K % 64), FO_ERR_UNSUPPORTED (tile shape
  * other than 256x128 / 256x256 / 64x64), FO_ERR_HIP (launch failure).
@@ -403,8 +404,8 @@ fo_status fo_reset_counters(uint32_t* counters, int32_t n, void* stream);
  * consumer grid and the sync modes at their built-in defaults consumes all
  * groups in one launch behind the GEMM, fused with the post-reorder (the same
  * values in dst and out, the counters as below):
- *   gemm_stream: reset kernel -> GEMM (signalling) -> done wait
- *   comm_stream: gate and wait for every counter -> consumer + post-reorder
+ *   gemm_stream: GEMM -> reset kernel (counters at their targets) -> done wait
+ *   comm_stream: gate kernel -> consumer + post-reorder
  *                [-> mark kernel, when its workgroups are too many to be counted]
  * The two streams hand work to each other on the device, not with events:
  * the reset kernel zeroes counters[0, P + FO_DISPENSER_WORDS), writes the

@@ -91,11 +91,6 @@ __device__ __forceinline__ void count_done(uint32_t* done, uint32_t done_tag) {
 hipError_t launch_done_wait(const uint32_t* done, uint32_t done_tag, int32_t blocks, uint32_t* status,
                             uint64_t timeout_ticks, hipStream_t s);
 hipError_t launch_gate(uint32_t* gate, uint32_t tag, uint32_t* status, uint64_t timeout_ticks, hipStream_t s);
-// The gate of a run whose groups are consumed together: behind the gate it
-// waits until every group counter j < groups has reached its target,
-// group_first[j + 1] - group_first[j] (device plan table).
-hipError_t launch_gate_all(uint32_t* gate, uint32_t tag, const uint32_t* counters, const int32_t* group_first,
-                           int32_t groups, uint32_t* status, uint64_t timeout_ticks, hipStream_t s);
 // One thread that counts as the only workgroup of a final launch, behind a
 // launch that does not count itself.
 hipError_t launch_mark_done(uint32_t* done, uint32_t done_tag, hipStream_t s);

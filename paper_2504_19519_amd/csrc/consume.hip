@@ -118,7 +118,9 @@ __global__ __launch_bounds__(64) void done_wait_kernel(const uint32_t* done, uin
 // timeout the lane raises bit 0 of the status word and, unless the word
 // already holds a later run's tag (which must not be held up), marks the
 // word (compare-and-swap, so a tag that arrives meanwhile still wins).
-__device__ __forceinline__ void pass_gate(uint32_t* gate, uint32_t tag, uint32_t* status, uint64_t timeout_ticks) {
+__global__ __launch_bounds__(64) void gate_kernel(uint32_t* gate, uint32_t tag, uint32_t* status,
+                                                  uint64_t timeout_ticks) {
+    if (threadIdx.x != 0) return;
     uint32_t v = __hip_atomic_load(gate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const uint64_t t0 = wall_clock64();
     while (v != tag) {
@@ -141,35 +143,6 @@ __device__ __forceinline__ void pass_gate(uint32_t* gate, uint32_t tag, uint32_t
         }
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-}
-
-__global__ __launch_bounds__(64) void gate_kernel(uint32_t* gate, uint32_t tag, uint32_t* status,
-                                                  uint64_t timeout_ticks) {
-    if (threadIdx.x == 0) pass_gate(gate, tag, status, timeout_ticks);
-}
-
-// The gate and the waits of a run whose groups are consumed together (one
-// wave): lane 0 passes the gate, then lane l polls the counters l, l + 64, ...
-// Bounded like wait_kernel.
-__global__ __launch_bounds__(64) void gate_all_kernel(uint32_t* gate, uint32_t tag, const uint32_t* counters,
-                                                      const int32_t* group_first, int32_t groups, uint32_t* status,
-                                                      uint64_t timeout_ticks) {
-    if (threadIdx.x == 0) pass_gate(gate, tag, status, timeout_ticks);
-    const uint64_t t0 = wall_clock64();
-    for (int j0 = 0; j0 < groups; j0 += 64) {
-        const int j = j0 + (int)threadIdx.x;
-        const bool mine = j < groups;
-        const uint32_t target = mine ? (uint32_t)(group_first[j + 1] - group_first[j]) : 0u;
-        const uint32_t* c = counters + (mine ? j : 0);
-        while (!__all(!mine || __hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= target)) {
-            __builtin_amdgcn_s_sleep(4);
-            if (wall_clock64() - t0 > timeout_ticks) {
-                if (threadIdx.x == 0 && status)
-                    __hip_atomic_fetch_or(status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                return;
-            }
-        }
-    }
 }
 
 // Counts a launch that ends with the kernel before this one on the stream.
@@ -574,13 +547,6 @@ hipError_t launch_done_wait(const uint32_t* done, uint32_t done_tag, int32_t blo
 
 hipError_t launch_gate(uint32_t* gate, uint32_t tag, uint32_t* status, uint64_t timeout_ticks, hipStream_t s) {
     hipLaunchKernelGGL(gate_kernel, dim3(1), dim3(64), 0, s, gate, tag, status, timeout_ticks);
-    return hipGetLastError();
-}
-
-hipError_t launch_gate_all(uint32_t* gate, uint32_t tag, const uint32_t* counters, const int32_t* group_first,
-                           int32_t groups, uint32_t* status, uint64_t timeout_ticks, hipStream_t s) {
-    hipLaunchKernelGGL(gate_all_kernel, dim3(1), dim3(64), 0, s, gate, tag, counters, group_first, groups, status,
-                       timeout_ticks);
     return hipGetLastError();
 }
 

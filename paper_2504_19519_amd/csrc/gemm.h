@@ -37,6 +37,10 @@ struct GemmArgs {
 hipError_t launch_gemm(int dtype, int tile_m, int tile_n, const GemmArgs& a, int grid, hipStream_t s);
 // Plans with 64x64 tiles (gemm_block.hip); wave_width: the plan's W.
 hipError_t launch_gemm64(int dtype, GemmArgs a, int wave_width, bool share_cus, hipStream_t s);
+// Plans with 256x128 and 256x256 tiles in 128x128 blocks (gemm_block.hip), and
+// whether a launch should take them.
+bool gemm_in_parts(int tile_n, const GemmArgs& a, int wave_width);
+hipError_t launch_gemm_parts(int dtype, int tile_n, GemmArgs a, int wave_width, bool share_cus, hipStream_t s);
 bool gemm_tile_supported(int tile_m, int tile_n);
 
 }  // namespace fo

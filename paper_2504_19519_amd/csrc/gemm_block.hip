@@ -1,5 +1,6 @@
-// GEMM of plans with 64x64 tiles (gfx950): the block that a workgroup computes
-// is chosen apart from the plan's tile.
+// GEMM in blocks that are chosen apart from the plan's tile (gfx950): every plan
+// with 64x64 tiles, and unsignalled launches of the larger tiles whose last wave
+// would be nearly empty (gemm_in_parts).
 //
 // A 64x64 tile is the only one that fits sizes which are odd multiples of 64,
 // but as a unit of computation it is a poor one: per 64 k values it brings
@@ -82,7 +83,7 @@ __device__ __forceinline__ int32_t table_at(const int32_t* t, int64_t i) {
     return ((const __attribute__((address_space(4))) int32_t*)(uintptr_t)t)[i];
 }
 
-template <int DT, int BM, int BN, int ST, int KS>
+template <int DT, int TM, int TN, int BM, int BN, int ST, int KS>
 __device__ __forceinline__ void block_body(const GemmArgs& a) {
     constexpr int kWaves = 4;                          // 2 x 2
     constexpr int WTM = BM / 2, WTN = BN / 2;          // a wave's part of the block
@@ -91,9 +92,8 @@ __device__ __forceinline__ void block_body(const GemmArgs& a) {
     constexpr int kStage = KS * kSlice;                // a stage holds KS slices
     constexpr int kAI = kA / 1024 / kWaves, kBI = BN * 128 / 1024 / kWaves;
     constexpr int kPer = kAI + kBI, kLoads = KS * kPer;      // loads per slice, per step
-    constexpr int kTile = 64;                          // the plan's tile
-    constexpr bool kOwnTile = WTM == kTile;            // a wave's part is a plan tile
-    static_assert((BM == 128 && BN == 128) || (BM <= kTile && BN <= kTile && BM >= 32 && BN >= 32),
+    constexpr bool kOwnTile = WTM == TM && WTN == TN;  // a wave's part is a plan tile (of TM x TN)
+    static_assert((kOwnTile || (TM % BM == 0 && TN % BN == 0)) && BM >= 32 && BN >= 32,
                   "a plan tile per wave, a plan tile, or part of one");
     static_assert(ST >= 2 && ST <= 4 && ST * kLoads <= 62, "stages");
 
@@ -282,7 +282,7 @@ __device__ __forceinline__ void block_body(const GemmArgs& a) {
         col0 = bn * BN + wn * WTN;
         inside = row0 < a.M && col0 < a.N;
         if (inside) {
-            const int tile = row0 / kTile * a.tiles_n + col0 / kTile;
+            const int tile = row0 / TM * a.tiles_n + col0 / TN;
             slot = a.tile_to_slot ? table_at(a.tile_to_slot, tile) : 0;
             group = a.slot_group ? table_at(a.slot_group, slot) : 0;
             if (a.pattern == FO_PATTERN_SUBTOKEN && lane < WTM) {
@@ -295,22 +295,22 @@ __device__ __forceinline__ void block_body(const GemmArgs& a) {
     // the wave's part, by pattern.
     auto find_rows = [&]() __attribute__((always_inline)) {
         if (!inside || lane >= WTM) return;
-        const int r = row0 % kTile + lane;
+        const int r = row0 % TM + lane;
         int64_t off;
         if (a.pattern == FO_PATTERN_ROWMAJOR) {
-            off = (int64_t)(row0 + lane) * a.N + col0 / kTile * kTile;
+            off = (int64_t)(row0 + lane) * a.N + col0 / TN * TN;
         } else if (a.pattern == FO_PATTERN_TILE) {
-            off = ((int64_t)slot * kTile + r) * kTile;
+            off = ((int64_t)slot * TM + r) * TN;
         } else if (a.pattern == FO_PATTERN_SUBTILE) {
-            const int h = kTile / a.num_dest;
+            const int h = TM / a.num_dest;
             const int k = r / h, rr = r - k * h;
             const int64_t f0 = table_at(a.group_first, group);
             const int64_t nj = table_at(a.group_first, group + 1) - f0;
-            off = f0 * kTile * kTile + ((int64_t)k * nj + (slot - f0)) * h * kTile + (int64_t)rr * kTile;
+            off = f0 * TM * TN + ((int64_t)k * nj + (slot - f0)) * h * TN + (int64_t)rr * TN;
         } else {
-            off = ((int64_t)a.pool_off[bucket] + a.pool_base[(int64_t)slot * a.num_dest + bucket] + rank) * kTile;
+            off = ((int64_t)a.pool_off[bucket] + a.pool_base[(int64_t)slot * a.num_dest + bucket] + rank) * TN;
         }
-        s_off[wave][lane] = off + col0 % kTile;
+        s_off[wave][lane] = off + col0 % TN;
     };
     // The counts of a block's plan tiles (Section 3.2), sent by the last of its
     // waves to have seen its own stores complete (the caller has waited for
@@ -470,27 +470,51 @@ __device__ __forceinline__ void block_body(const GemmArgs& a) {
 }
 
 // Template arguments: dtype, block rows and columns, waves, stages, k values
-// per step.
-template <int DT, int BM, int BN, int WM, int WN, int ST, int BK>
+// per step, plan tile.
+template <int DT, int BM, int BN, int WM, int WN, int ST, int BK, int TM, int TN>
 __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_signal_kernel(const GemmArgs a) {
     static_assert(WM == 2 && WN == 2 && BK % 64 == 0, "2 x 2 waves");
-    block_body<DT, BM, BN, ST, BK / 64>(a);
+    block_body<DT, TM, TN, BM, BN, ST, BK / 64>(a);
+}
+
+// 128x128 blocks of plan tiles TM x TN, one or two on a compute unit.
+template <int DT, int TM, int TN>
+void launch_128(const GemmArgs& a, int grid, bool pair, hipStream_t s) {
+    if (pair)
+        hipLaunchKernelGGL((gemm_signal_kernel<DT, 128, 128, 2, 2, 2, 64, TM, TN>), dim3(grid), dim3(256), 0, s, a);
+    else
+        hipLaunchKernelGGL((gemm_signal_kernel<DT, 128, 128, 2, 2, 3, 64, TM, TN>), dim3(grid), dim3(256), 0, s, a);
 }
 
 // Stages and steps as measured (bf16, us per launch, three operand sets in
-// turn): 128x128, 3 stages of 64 (768x3840x4160 29.0; 4 stages 29.3, 2 stages
-// 43.7: a step's loads then have less than a step to land); 64x64, 4 of 64,
-// two blocks on a compute unit (64x4096x3584 14.2; 3 stages 16.6; 3 of 128
-// 14.8 but one block per unit); the small blocks, steps of 128, since their
-// MFMAs are too few to cover a barrier per 64 (64x32 128x4096x3584 12.6, in
-// steps of 64 15.7; 32x32 64x4096x3584 9.8, 11.2).
+// turn): 128x128 alone on its compute unit, 3 stages of 64 (768x3840x4160 29.0; 4
+// stages 29.3, 2 stages 43.7: a step's loads then have less than a step to
+// land), two on a unit, 2 stages; 64x64, 4 of 64, two on a unit (64x4096x3584
+// 14.2; 3 stages 16.6; 3 of 128 14.8 but one block per unit); the small blocks,
+// steps of 128, since their MFMAs are too few to cover a barrier per 64 (64x32
+// 128x4096x3584 12.6, in steps of 64 15.7; 32x32 64x4096x3584 9.8, 11.2).
 template <int DT>
-void launch_dt(const GemmArgs& a, int bm, int bn, int grid, hipStream_t s) {
+void launch_64(const GemmArgs& a, int bm, int bn, int grid, bool pair, hipStream_t s) {
     const dim3 g(grid), b(256);
-    if (bm == 128) hipLaunchKernelGGL((gemm_signal_kernel<DT, 128, 128, 2, 2, 3, 64>), g, b, 0, s, a);
-    else if (bm == 64 && bn == 64) hipLaunchKernelGGL((gemm_signal_kernel<DT, 64, 64, 2, 2, 4, 64>), g, b, 0, s, a);
-    else if (bm == 64) hipLaunchKernelGGL((gemm_signal_kernel<DT, 64, 32, 2, 2, 3, 128>), g, b, 0, s, a);
-    else hipLaunchKernelGGL((gemm_signal_kernel<DT, 32, 32, 2, 2, 4, 128>), g, b, 0, s, a);
+    if (bm == 128) launch_128<DT, 64, 64>(a, grid, pair, s);
+    else if (bm == 64 && bn == 64)
+        hipLaunchKernelGGL((gemm_signal_kernel<DT, 64, 64, 2, 2, 4, 64, 64, 64>), g, b, 0, s, a);
+    else if (bm == 64) hipLaunchKernelGGL((gemm_signal_kernel<DT, 64, 32, 2, 2, 3, 128, 64, 64>), g, b, 0, s, a);
+    else hipLaunchKernelGGL((gemm_signal_kernel<DT, 32, 32, 2, 2, 4, 128, 64, 64>), g, b, 0, s, a);
+}
+
+// Whether 128x128 blocks run in pairs on a compute unit. A pair takes about 1.7
+// times a single block's time (its two stages hide less, its two workgroups
+// cover each other's barriers, prologues and epilogues), so it pays where it
+// saves enough rounds (bf16 us, single / pair, blocks in W): 1.1 W K 2048
+// 32.9 / 27.2; 2.2 W K 1920 49.9 / 51.4, K 1024 31.8 / 28.5; 3 W K 5440
+// 151 / 156; 4 W K 4032 145 / 138; 4.4 W K 320 30.5 / 22.0. Signalled, a second
+// round of a pair draws its positions one by one from the same line: one round
+// only (1.1 W 34.8 / 27.6; 4.4 W K 320 34.9 / 38.5).
+bool in_pairs(const GemmArgs& a, int64_t blocks, int64_t W, bool share_cus) {
+    if (!share_cus || blocks <= W) return false;
+    if (a.counters) return blocks <= 2 * W;
+    return a.K <= 1024 || 17 * ((blocks + 2 * W - 1) / (2 * W)) < 10 * ((blocks + W - 1) / W);
 }
 
 }  // namespace
@@ -505,9 +529,9 @@ void launch_dt(const GemmArgs& a, int bm, int bn, int grid, hipStream_t s) {
 //   above          128x128 720 tiles, K 4160: 29.0 (64x64 38.5);
 //                          2272 tiles, K 1920: 48.7 (57.2)
 // Parts of a tile have no count of their own: a signalled launch takes whole
-// tiles. Two 64x64 blocks share a compute unit unless the plan reserves units
-// for communication (a second block would be placed on those). A traced launch
-// runs in tiles, one per dispatch position.
+// tiles. Two blocks share a compute unit only if the plan reserves no units for
+// communication (a second block would be placed on those). A traced launch runs
+// in tiles, one per dispatch position.
 hipError_t launch_gemm64(int dtype, GemmArgs a, int wave_width, bool share_cus, hipStream_t s) {
     const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n, W = wave_width;
     int bm = 64, bn = 64;
@@ -522,11 +546,46 @@ hipError_t launch_gemm64(int dtype, GemmArgs a, int wave_width, bool share_cus, 
     // the same number of output rows per band as in the plan's order
     a.block_band = bm == 128 ? (a.group_m + 1) / 2 : bm == 32 ? 2 * a.group_m : a.group_m;
     const int64_t blocks = (int64_t)a.blocks_m * a.blocks_n;
-    const int per_cu = bm == 64 && bn == 64 && share_cus && !a.trace ? 2 : 1;
-    const int grid = (int)std::min<int64_t>(blocks, W * per_cu);
+    const bool pair = bm == 128 ? in_pairs(a, blocks, W, share_cus) : bn == 64 && share_cus && !a.trace;
+    const int grid = (int)std::min<int64_t>(blocks, pair ? 2 * W : W);
     a.num_dispensers = std::max(1, std::min(a.num_dispensers, grid));
-    if (dtype == FO_FP16) launch_dt<FO_FP16>(a, bm, bn, grid, s);
-    else launch_dt<FO_BF16>(a, bm, bn, grid, s);
+    if (dtype == FO_FP16) launch_64<FO_FP16>(a, bm, bn, grid, pair, s);
+    else launch_64<FO_BF16>(a, bm, bn, grid, pair, s);
+    return hipGetLastError();
+}
+
+// 128x128 blocks instead of whole larger tiles (unsignalled launches only: a
+// part has no count), where the tiles' last wave is emptier than the blocks' or
+// one tile per compute unit covers its barriers less than a pair of blocks
+// (bf16, us per launch, K 4096 / 1024, tiles -> blocks):
+//   256x128  0.5 W  52 -> 32 / 18 -> 12    0.75 W  55 -> 48 / 19 -> 17
+//            W      60 -> 57 / 20 -> 18    1.25 W 107 -> 85 / 34 -> 28
+//            2 W   121 -> 119 / 37 -> 34   (8 W, K 3584: 430 us in tiles, 480 by
+//            the rate of 4 W in blocks: the clock is power-limited there and the
+//            larger tile reads less per flop)
+//   256x256  0.25 W 72 -> 33 / 25 -> 13    0.5 W   74 -> 57 / 26 -> 19
+//            0.75 W 82 -> 90 / 28 -> 29    W      101 -> 119 / 32 -> 34
+//            1.25 W 168 -> 158 / 52 -> 45  1.5 W  178 -> 182 / 55 -> 51
+//            1.75 W 190 -> 214 / 57 -> 59
+bool gemm_in_parts(int tile_n, const GemmArgs& a, int wave_width) {
+    if (a.counters || a.trace) return false;
+    const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n, W = wave_width;
+    if (tile_n == 128) return tiles <= 2 * W;
+    return 2 * tiles <= W || (tiles > W && (4 * tiles <= 5 * W || (a.K <= 1024 && 2 * tiles <= 3 * W)));
+}
+
+hipError_t launch_gemm_parts(int dtype, int tile_n, GemmArgs a, int wave_width, bool share_cus, hipStream_t s) {
+    a.blocks_m = (int)(a.M / 128);
+    a.blocks_n = (int)(a.N / 128);
+    a.block_band = 2 * a.group_m;
+    a.num_dispensers = 1;
+    const int64_t blocks = (int64_t)a.blocks_m * a.blocks_n, W = wave_width;
+    const bool pair = in_pairs(a, blocks, W, share_cus);
+    const int grid = (int)std::min<int64_t>(blocks, pair ? 2 * W : W);
+    if (dtype == FO_FP16 && tile_n == 128) launch_128<FO_FP16, 256, 128>(a, grid, pair, s);
+    else if (dtype == FO_FP16) launch_128<FO_FP16, 256, 256>(a, grid, pair, s);
+    else if (tile_n == 128) launch_128<FO_BF16, 256, 128>(a, grid, pair, s);
+    else launch_128<FO_BF16, 256, 256>(a, grid, pair, s);
     return hipGetLastError();
 }
 

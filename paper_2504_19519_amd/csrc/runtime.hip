@@ -136,13 +136,14 @@ __global__ void fill_u32_kernel(uint32_t* p, int32_t n, uint32_t v) {
 // kernel on the consumer stream waits for). If a gate of this run timed out
 // before, the word holds the tag's timed-out mark: the status word then gets
 // bit 0 (the status word is never cleared here: its bits are sticky).
-// gate == NULL: only the zeroing.
-__global__ __launch_bounds__(256) void reset_run_kernel(uint32_t* counters, int32_t n, uint32_t* done,
-                                                        uint32_t done_tag, uint32_t* status, uint32_t* gate,
-                                                        uint32_t tag) {
-    for (int i = threadIdx.x; i < n; i += blockDim.x) counters[i] = 0u;
-    if (done && threadIdx.x < kDoneWords) done[threadIdx.x * kDoneStride] = done_tag;
-    if (!gate) return;
+// group_first (device plan table) non-null: the launch follows the run's GEMM,
+// every group is complete, and the `groups` counters get their targets.
+__global__ __launch_bounds__(256) void reset_run_kernel(uint32_t* counters, int32_t n, const int32_t* group_first,
+                                                        int32_t groups, uint32_t* done, uint32_t done_tag,
+                                                        uint32_t* status, uint32_t* gate, uint32_t tag) {
+    for (int i = threadIdx.x; i < n; i += blockDim.x)
+        counters[i] = group_first && i < groups ? (uint32_t)(group_first[i + 1] - group_first[i]) : 0u;
+    if (threadIdx.x < kDoneWords) done[threadIdx.x * kDoneStride] = done_tag;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -437,9 +438,12 @@ fo_status fo_gemm_signal_reorder(const fo_plan* plan, const void* dev_plan, cons
         a.num_dispensers = plan->order == FO_ORDER_XCD ? std::min(plan->num_xcds, FO_DISPENSER_WORDS) : 1;
         a.num_dispensers = std::max(1, std::min(a.num_dispensers, grid));
     }
+    const int width = std::max(plan->W, 1);
     hipError_t e = plan->tile_m == 64
-                       ? fo::launch_gemm64(plan->dtype, a, std::max(plan->W, 1), plan->reserved_cus == 0,
-                                             (hipStream_t)stream)
+                       ? fo::launch_gemm64(plan->dtype, a, width, plan->reserved_cus == 0, (hipStream_t)stream)
+                   : fo::gemm_in_parts(plan->tile_n, a, width)
+                       ? fo::launch_gemm_parts(plan->dtype, plan->tile_n, a, width, plan->reserved_cus == 0,
+                                               (hipStream_t)stream)
                        : fo::launch_gemm(plan->dtype, plan->tile_m, plan->tile_n, a, grid, (hipStream_t)stream);
     return e == hipSuccess ? FO_OK : fo::hip_fail("GEMM launch", e);
 }
@@ -536,16 +540,21 @@ fo_status fo_run_overlapped(const fo_plan* plan, const void* dev_plan, const voi
         post.peer = static_cast<const uint16_t*>(peer);
         post.bytes = (uint32_t)bytes;
     }
-    if (overlap) {
+    // Hands the run over to the consumer stream: ahead of the GEMM, with the
+    // counters zeroed, or (groups consumed together) behind it, with the counters
+    // at their targets.
+    auto hand_over = [&]() -> fo_status {
         hipLaunchKernelGGL(fo::reset_run_kernel, dim3(1), dim3(256), 0, s1, counters, plan->P + FO_DISPENSER_WORDS,
-                           done, done_tag, status_word, gate, tag);
+                           fused ? post.group_first : nullptr, plan->P, done, done_tag, status_word, gate, tag);
         if ((e = hipGetLastError()) != hipSuccess) return fo::hip_fail("reset kernel launch", e);
-    }
-    if (overlap && !fused && (e = fo::launch_gate(gate, tag, status_word, ticks, s2)) != hipSuccess)
-        return fo::hip_fail("gate kernel launch", e);
+        if ((e = fo::launch_gate(gate, tag, status_word, ticks, s2)) != hipSuccess)
+            return fo::hip_fail("gate kernel launch", e);
+        return FO_OK;
+    };
+    if (overlap && !fused && (st = hand_over()) != FO_OK) return st;
     if (gemm_begin_event && (e = hipEventRecord((hipEvent_t)gemm_begin_event, s1)) != hipSuccess)
         return fo::hip_fail("hipEventRecord", e);
-    if ((st = fo_gemm_signal_reorder(plan, dev_plan, A, W, C_out, overlap ? counters : nullptr, s1, &o)) !=
+    if ((st = fo_gemm_signal_reorder(plan, dev_plan, A, W, C_out, overlap && !fused ? counters : nullptr, s1, &o)) !=
         FO_OK)
         return st;
     if (gemm_end_event && (e = hipEventRecord((hipEvent_t)gemm_end_event, s1)) != hipSuccess)
@@ -555,13 +564,10 @@ fo_status fo_run_overlapped(const fo_plan* plan, const void* dev_plan, const voi
         return e == hipSuccess ? FO_OK : fo::hip_fail("post-reorder launch", e);
     }
     if (fused) {
-        // one wait for all counters (behind the GEMM launch, which may have been
-        // refused) and one launch for all groups, counted by its own workgroups or, when they
+        // one launch for all groups, counted by its own workgroups or, when they
         // are many (about 60 ns each for the read and the add on one of the done
         // words), by a kernel of one thread behind it
-        if ((e = fo::launch_gate_all(gate, tag, counters, post.group_first, plan->P, status_word, ticks, s2)) !=
-            hipSuccess)
-            return fo::hip_fail("gate kernel launch", e);
+        if ((st = hand_over()) != FO_OK) return st;
         const bool mark = fo::post_form(post, true).blocks > 512;
         if (!mark) {
             post.done = done;

@@ -56,3 +56,39 @@ def test_block_forms(dtype, K):
                     c = counters.cpu().numpy()
                     np.testing.assert_array_equal(c[:plan.P], np.array(o.targets), err_msg=what)
                     np.testing.assert_array_equal(c[plan.P:plan.P + fo.DISPENSER_WORDS], 0, err_msg=what)
+
+
+@pytest.mark.parametrize("tile_n,widths", [(128, [12, 11, 5, 4]), (256, [24, 12, 11, 5, 4])])
+@pytest.mark.parametrize("dtype,K", [("fp16", 64), ("bf16", 192), ("fp16", 448)])
+def test_parts_of_larger_tiles(tile_n, widths, dtype, K):
+    # 6 tiles of 256 x tile_n: unsignalled launches take 128x128 blocks where
+    # the last wave is emptier in whole tiles (at most W / 2, and just past W),
+    # signalled ones whole tiles; the bits are the same
+    torch = torch_mod()
+    M, N = 512, 3 * tile_n
+    say(f"[gemm parts] {M}x{N}x{K} tile 256x{tile_n} {dtype}")
+    rng = np.random.default_rng(K)
+    A = workloads.to_bits(rng.uniform(-1, 1, (M, K)), dtype)
+    W = workloads.to_bits(rng.uniform(-1, 1, (N, K)) / np.sqrt(K), dtype)
+    dA, dW = to_dev(A), to_dev(W)
+    plain = None
+    for cus in widths:
+        for pattern, nd in [("rowmajor", 0), ("tile", 0), ("subtile", 4), ("subtoken", 3)]:
+            sigma = rng.permutation(nd) if pattern == "subtile" else None
+            bucket = rng.integers(0, nd, M) if pattern == "subtoken" else None
+            sizes = [1] * -(-6 // cus)
+            plan = fo.plan_groups(M, N, K, dtype=dtype, tile_m=256, tile_n=tile_n, num_cus=cus, pattern=pattern,
+                                  num_dest=nd, dest_perm=sigma, row_bucket=bucket, sizes=sizes)
+            o = oracle.make_plan(M, N, 256, tile_n, num_cus=cus, order="xcd", group_m=4, num_xcds=8, pattern=pattern,
+                                 num_dest=nd, sigma=sigma, bucket=bucket, sizes=sizes, unit="waves")
+            dp = dev_plan(plan)
+            for counters in (None, zeros_u32(plan.num_counters)):
+                C = empty16(M * N, dtype)
+                fo.gemm_signal_reorder(plan, dp, dA, dW, C, counters)
+                torch.cuda.synchronize()
+                got = from_dev(C)[:M * N]
+                if plain is None:
+                    plain = got
+                    assert_close_bits(got, oracle.gemm_ref(A, W, dtype).reshape(-1), dtype, "GEMM")
+                np.testing.assert_array_equal(got, plain[oracle.reorder_index(o)],
+                                              err_msg=f"W={cus} {pattern} {'signalled' if counters is not None else ''}")
