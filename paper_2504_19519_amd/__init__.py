@@ -154,29 +154,37 @@ def _check(status: int) -> None:
 def _ptr(x) -> Optional[int]:
     if x is None:
         return None
+    get = getattr(x, "data_ptr", None)
+    if get is not None:
+        return int(get())
     if isinstance(x, (int, np.integer)):
         return int(x) or None
-    if hasattr(x, "data_ptr"):
-        return int(x.data_ptr())
     raise TypeError(f"cannot take a device pointer of {type(x)}")
 
 
-def _need(x, nbytes: int, what: str) -> None:
-    """A tensor argument must hold at least `nbytes` (raw pointers are taken
-    as given: the C ABI cannot see buffer sizes)."""
-    if x is not None and hasattr(x, "numel") and hasattr(x, "element_size"):
-        have = int(x.numel()) * int(x.element_size())
+def _buf(x, nbytes: int, what: str) -> Optional[int]:
+    """The device pointer of an argument. A tensor must hold at least `nbytes`
+    (raw pointers are taken as given: the C ABI cannot see buffer sizes)."""
+    if x is None:
+        return None
+    get = getattr(x, "data_ptr", None)
+    if get is None:
+        return _ptr(x)
+    if hasattr(x, "numel") and hasattr(x, "element_size"):
+        have = x.numel() * x.element_size()
         if have < nbytes:
             raise ValueError(f"{what}: {have} bytes, the call needs {nbytes}")
+    return int(get())
 
 
 def _stream(s) -> Optional[int]:
     if s is None:
         return None
+    handle = getattr(s, "cuda_stream", None)
+    if handle is not None:
+        return int(handle) or None
     if isinstance(s, (int, np.integer)):
         return int(s) or None
-    if hasattr(s, "cuda_stream"):
-        return int(s.cuda_stream) or None
     raise TypeError(f"cannot take a stream handle of {type(s)}")
 
 
@@ -215,6 +223,13 @@ class Plan:
         self._h = ctypes.c_void_p(handle)
         self.M, self.N, self.K, self.dtype = M, N, K, dtype
         self.tile_m, self.tile_n, self.pattern, self.num_dest = tile_m, tile_n, pattern, num_dest
+        # bytes of the calls' buffers, asked of the library once (a plan does
+        # not change): every call checks its arguments against them
+        L = lib()
+        self._a, self._w, self._c, self._n = 2 * M * K, 2 * N * K, 2 * M * N, 2 * N
+        self._dst = 2 * L.fo_plan_dest_elems(self._h)
+        self._counters = 4 * L.fo_plan_num_counters(self._h)
+        self._gemm_counters = 4 * (L.fo_plan_num_groups(self._h) + DISPENSER_WORDS)
 
     def __del__(self):
         h = getattr(self, "_h", None)
@@ -429,32 +444,27 @@ def _opts(o):
 
 
 def gemm_signal_reorder(plan: Plan, dev_plan, A, W, C_out, counters=None, stream=None, opts=None) -> None:
-    _need(A, 2 * plan.M * plan.K, "A")
-    _need(W, 2 * plan.N * plan.K, "W")
-    _need(C_out, 2 * plan.M * plan.N, "C_out")
-    _need(counters, 4 * (plan.P + DISPENSER_WORDS), "counters")
-    _check(lib().fo_gemm_signal_reorder(plan.handle, _ptr(dev_plan), _ptr(A), _ptr(W), _ptr(C_out),
-                                        _ptr(counters), _stream(stream), _opts(opts)))
+    _check(lib().fo_gemm_signal_reorder(plan._h, _ptr(dev_plan), _buf(A, plan._a, "A"), _buf(W, plan._w, "W"),
+                                        _buf(C_out, plan._c, "C_out"),
+                                        _buf(counters, plan._gemm_counters, "counters"), _stream(stream),
+                                        _opts(opts)))
 
 
 def consume_group(src, peer, dst, length: int, dtype, counter=None, target: int = 0,
                   status_word=None, stream=None, opts=None) -> None:
-    _need(src, 2 * int(length), "src")
-    _need(peer, 2 * int(length), "peer")
-    _need(dst, 2 * int(length), "dst")
-    _check(lib().fo_consume_group(_ptr(src), _ptr(peer), _ptr(dst), int(length), _DTYPES[dtype],
-                                  _ptr(counter), int(target), _ptr(status_word), _stream(stream),
+    n = int(length)
+    _check(lib().fo_consume_group(_buf(src, 2 * n, "src"), _buf(peer, 2 * n, "peer"), _buf(dst, 2 * n, "dst"), n,
+                                  _DTYPES[dtype], _ptr(counter), int(target), _ptr(status_word), _stream(stream),
                                   _opts(opts)))
 
 
 def post_reorder(plan: Plan, dev_plan, src, out, bias=None, gamma=None, eps: float = 1e-6,
                  do_rmsnorm: bool = False, stream=None) -> None:
-    _need(src, 2 * (plan.dest_elems if plan.pattern != ROWMAJOR else plan.M * plan.N), "src")
-    _need(out, 2 * plan.M * plan.N, "out")
-    _need(bias, 2 * plan.N, "bias")
-    _need(gamma, 2 * plan.N, "gamma")
-    _check(lib().fo_post_reorder(plan.handle, _ptr(dev_plan), _ptr(src), _ptr(out), _ptr(bias),
-                                 _ptr(gamma), float(eps), int(bool(do_rmsnorm)), _stream(stream)))
+    _check(lib().fo_post_reorder(plan._h, _ptr(dev_plan),
+                                 _buf(src, plan._dst if plan.pattern != ROWMAJOR else plan._c, "src"),
+                                 _buf(out, plan._c, "out"), _buf(bias, plan._n, "bias"),
+                                 _buf(gamma, plan._n, "gamma"), float(eps), 1 if do_rmsnorm else 0,
+                                 _stream(stream)))
 
 
 def reset_counters(counters, n: int, stream=None) -> None:
@@ -465,21 +475,14 @@ def run_overlapped(plan: Plan, dev_plan, A, W, C_out, peer, dst, out=None, bias=
                    eps: float = 1e-6, do_rmsnorm: bool = False, counters=None, status_word=None,
                    gemm_stream=None, comm_stream=None, gemm_begin_event=None,
                    gemm_end_event=None, opts=None) -> None:
-    _need(A, 2 * plan.M * plan.K, "A")
-    _need(W, 2 * plan.N * plan.K, "W")
-    _need(C_out, 2 * plan.M * plan.N, "C_out")
-    _need(peer, 2 * plan.M * plan.N, "peer")
-    _need(dst, 2 * plan.dest_elems, "dst")
-    _need(out, 2 * plan.M * plan.N, "out")
-    _need(bias, 2 * plan.N, "bias")
-    _need(gamma, 2 * plan.N, "gamma")
-    _need(counters, 4 * plan.num_counters, "counters")
-    _need(status_word, 4, "status_word")
-    _check(lib().fo_run_overlapped(plan.handle, _ptr(dev_plan), _ptr(A), _ptr(W), _ptr(C_out),
-                                   _ptr(peer), _ptr(dst), _ptr(out), _ptr(bias), _ptr(gamma),
-                                   float(eps), int(bool(do_rmsnorm)), _ptr(counters),
-                                   _ptr(status_word), _stream(gemm_stream), _stream(comm_stream),
-                                   _event(gemm_begin_event), _event(gemm_end_event), _opts(opts)))
+    _check(lib().fo_run_overlapped(plan._h, _ptr(dev_plan), _buf(A, plan._a, "A"), _buf(W, plan._w, "W"),
+                                   _buf(C_out, plan._c, "C_out"), _buf(peer, plan._c, "peer"),
+                                   _buf(dst, plan._dst, "dst"), _buf(out, plan._c, "out"),
+                                   _buf(bias, plan._n, "bias"), _buf(gamma, plan._n, "gamma"), float(eps),
+                                   1 if do_rmsnorm else 0, _buf(counters, plan._counters, "counters"),
+                                   _buf(status_word, 4, "status_word"), _stream(gemm_stream),
+                                   _stream(comm_stream), _event(gemm_begin_event), _event(gemm_end_event),
+                                   _opts(opts)))
 
 
 NOALLOC_MAX_COUNTERS = 1024    # FO_NOALLOC_MAX_COUNTERS
@@ -491,19 +494,13 @@ def run_overlapped_noalloc(plan: Plan, dev_plan, A, W, C_out, peer, dst, out=Non
     """fo_run_overlapped_noalloc: the overlapped run with the library's static
     counters array (no device allocation; calls on one device must not
     overlap)."""
-    _need(A, 2 * plan.M * plan.K, "A")
-    _need(W, 2 * plan.N * plan.K, "W")
-    _need(C_out, 2 * plan.M * plan.N, "C_out")
-    _need(peer, 2 * plan.M * plan.N, "peer")
-    _need(dst, 2 * plan.dest_elems, "dst")
-    _need(out, 2 * plan.M * plan.N, "out")
-    _need(bias, 2 * plan.N, "bias")
-    _need(gamma, 2 * plan.N, "gamma")
-    _need(status_word, 4, "status_word")
-    _check(lib().fo_run_overlapped_noalloc(plan.handle, _ptr(dev_plan), _ptr(A), _ptr(W), _ptr(C_out),
-                                           _ptr(peer), _ptr(dst), _ptr(out), _ptr(bias), _ptr(gamma),
-                                           float(eps), int(bool(do_rmsnorm)), _ptr(status_word),
-                                           _stream(gemm_stream), _stream(comm_stream), _opts(opts)))
+    _check(lib().fo_run_overlapped_noalloc(plan._h, _ptr(dev_plan), _buf(A, plan._a, "A"),
+                                           _buf(W, plan._w, "W"), _buf(C_out, plan._c, "C_out"),
+                                           _buf(peer, plan._c, "peer"), _buf(dst, plan._dst, "dst"),
+                                           _buf(out, plan._c, "out"), _buf(bias, plan._n, "bias"),
+                                           _buf(gamma, plan._n, "gamma"), float(eps), 1 if do_rmsnorm else 0,
+                                           _buf(status_word, 4, "status_word"), _stream(gemm_stream),
+                                           _stream(comm_stream), _opts(opts)))
 
 
 SYNC_FENCE_ALL, SYNC_FENCE_ONE, SYNC_COHERENT = 0, 1, 2
