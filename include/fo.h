@@ -484,8 +484,8 @@ fo_status fo_run_overlapped(const fo_plan* plan, const void* dev_plan,
  * allocates nothing and calls no allocating routine; the caller passes the
  * inputs and outputs as for fo_run_overlapped (status_word included: it is
  * an output, sticky as there), no events. Each run's reset kernel clears what
- * must start at zero (the group and position counters); the gate word keeps
- * the last run's tag. Every call on one device shares that device's array:
+ * must start at zero (the group and position counters); the gate word is
+ * cleared when the run has ended. Every call on one device shares that device's array:
  * calls that may overlap on one device (other streams, other threads) race
  * and must not be issued; calls queued on the same pair of streams are
  * ordered by the streams and are fine.

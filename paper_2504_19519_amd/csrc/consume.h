@@ -87,8 +87,9 @@ __device__ __forceinline__ void count_done(uint32_t* done, uint32_t done_tag) {
 }
 #endif
 // One wave that polls the done words until word k reaches done_tag plus
-// done_share(blocks, k) for every k (bounded like launch_wait).
-hipError_t launch_done_wait(const uint32_t* done, uint32_t done_tag, int32_t blocks, uint32_t* status,
+// done_share(blocks, k) for every k (bounded like launch_wait), then clears the
+// gate word.
+hipError_t launch_done_wait(const uint32_t* done, uint32_t done_tag, int32_t blocks, uint32_t* gate, uint32_t* status,
                             uint64_t timeout_ticks, hipStream_t s);
 hipError_t launch_gate(uint32_t* gate, uint32_t tag, uint32_t* status, uint64_t timeout_ticks, hipStream_t s);
 // One thread that counts as the only workgroup of a final launch, behind a

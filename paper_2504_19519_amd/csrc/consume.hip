@@ -93,9 +93,11 @@ __global__ __launch_bounds__(64) void wait_kernel(const uint32_t* counter, uint3
 // End handoff of an overlapped run (one wave, on the GEMM stream ahead of the
 // post-reorder): lane k < kDoneWords polls done word k until it reaches the
 // run's tag plus its share of the final launch's workgroups; the wave ends
-// when every lane's word has. Bounded like wait_kernel.
+// when every lane's word has. Then the gate word is cleared: a captured run that
+// is replayed brings the same tag again and must not find it there. Bounded like
+// wait_kernel (a timed-out wait leaves the gate word alone).
 __global__ __launch_bounds__(64) void done_wait_kernel(const uint32_t* done, uint32_t done_tag, int32_t blocks,
-                                                       uint32_t* status, uint64_t timeout_ticks) {
+                                                       uint32_t* gate, uint32_t* status, uint64_t timeout_ticks) {
     const int k = threadIdx.x;
     const bool mine = k < kDoneWords;
     const uint32_t target = done_tag + done_share(blocks, k);
@@ -108,6 +110,7 @@ __global__ __launch_bounds__(64) void done_wait_kernel(const uint32_t* done, uin
             return;
         }
     }
+    if (k == 0) __hip_atomic_store(gate, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Start handoff of an overlapped run (one wave, on the consumer stream ahead
@@ -539,9 +542,10 @@ hipError_t launch_wait(const uint32_t* counter, uint32_t target, uint32_t* statu
     return hipGetLastError();
 }
 
-hipError_t launch_done_wait(const uint32_t* done, uint32_t done_tag, int32_t blocks, uint32_t* status,
+hipError_t launch_done_wait(const uint32_t* done, uint32_t done_tag, int32_t blocks, uint32_t* gate, uint32_t* status,
                             uint64_t timeout_ticks, hipStream_t s) {
-    hipLaunchKernelGGL(done_wait_kernel, dim3(1), dim3(64), 0, s, done, done_tag, blocks, status, timeout_ticks);
+    hipLaunchKernelGGL(done_wait_kernel, dim3(1), dim3(64), 0, s, done, done_tag, blocks, gate, status,
+                       timeout_ticks);
     return hipGetLastError();
 }
 

@@ -578,7 +578,7 @@ fo_status fo_run_overlapped(const fo_plan* plan, const void* dev_plan, const voi
         if (mark && (e = fo::launch_mark_done(done, done_tag, s2)) != hipSuccess)
             return fo::hip_fail("mark kernel launch", e);
         const int blocks = mark ? 1 : (int)fo::post_form(post, true).blocks;
-        e = fo::launch_done_wait(done, done_tag, blocks, status_word, ticks, s1);
+        e = fo::launch_done_wait(done, done_tag, blocks, gate, status_word, ticks, s1);
         return e == hipSuccess ? FO_OK : fo::hip_fail("wait kernel launch", e);
     }
     // One consumer launch per group (more if a group has more pieces than a
@@ -630,7 +630,7 @@ fo_status fo_run_overlapped(const fo_plan* plan, const void* dev_plan, const voi
     // grid only through this run's final consumer (a late consumer of an
     // earlier run finds another tag in them and does not count)
     if (final_blocks > 0 &&
-        (e = fo::launch_done_wait(done, done_tag, final_blocks, status_word, ticks, s1)) != hipSuccess)
+        (e = fo::launch_done_wait(done, done_tag, final_blocks, gate, status_word, ticks, s1)) != hipSuccess)
         return fo::hip_fail("wait kernel launch", e);
     if (out) return fo_post_reorder(plan, dev_plan, dst, out, bias, gamma, eps, do_rmsnorm, s1);
     return FO_OK;
