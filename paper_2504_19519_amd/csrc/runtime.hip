@@ -266,12 +266,12 @@ bool plain_consumer(const fo_options& o) {
 // it saves behind it, and every group costs a wait kernel and a launch, while
 // consumed together the groups share one pass with the post-reorder. Measured
 // (us per run, a launch per group / together):
-//   256x256x256    4 groups   49 / 20      4096x7168x2048   2 groups  148 / 130
-//   1216x2880x1984 4 groups   60 / 33      8192x4096x4096   2 groups  254 / 250
-//   4096x4096x4096 2 groups  170 / 146     8192x8192x1024   3 groups  290 / 213
-//   16384x8192x2048 4 groups 610 / 598     8192x8192x3584   3 groups  459 / 451
-//   16384x4096x3584 4 groups 446 / 446     32768x4096x3584  4 groups  877 / 889
-//   8192x8192x7168 4 groups  755 / 768
+//   256x256x256     4 groups  49 / 19     4096x7168x2048  2 groups  146 / 128
+//   1216x2880x1984  4 groups  60 / 32     8192x4096x4096  2 groups  253 / 248
+//   4096x4096x4096  2 groups 168 / 136    8192x8192x1024  3 groups  290 / 207
+//   16384x8192x2048 4 groups 611 / 591    8192x8192x3584  3 groups  456 / 447
+//   16384x4096x3584 4 groups 442 / 445    32768x4096x3584 4 groups  869 / 878
+//   8192x8192x7168  4 groups 747 / 763
 // A launch per group pays once the GEMM (at the 5.5 TFLOP/s that a compute unit
 // reaches) lasts 300 us and three times as long as the consumer alone (at 5.1
 // TB/s): below that the groups after the first still run when the GEMM ends.
