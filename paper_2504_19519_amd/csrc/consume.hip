@@ -329,20 +329,24 @@ __device__ __forceinline__ void stream_coherent16(const uint16_t* __restrict__ s
 // per compute unit, so what it streams is what that wave keeps in flight over a
 // memory latency; the registers that a GEMM wave leaves it hold 4 KB, the LDS
 // beside a GEMM workgroup 24 KB. Direct-to-LDS loads (sc1 and nontemporal, as
-// in stream_coherent16) run D batches of 128 chunks ahead; the wave waits for
-// the oldest batch only, adds the peer's, stores, and loads the batch D further
+// in stream_coherent16) run D rounds of 4 KB ahead; the wave waits for
+// the oldest round only, adds the peer's, stores, and loads the batch D further
 // on in its place. A batch past the wave's last one is loaded through an empty
 // resource, so that every round has the same number of operations in flight.
 // Alone, 256 workgroups (us, register path -> ring; floor at 5.1 TB/s): sum of
 // 8388613 fp16 23.7 -> 12.5 (9.9) with its wait kernel, copy of 29360128 38.9 ->
-// 26.3 (23.0); rings of 8 and 16 KB: 16.7 and 13.2, 27.6 and 26.0. Beside the
+// 20.2 (23.0; part of it is in the memory-side cache). A round costs its wait,
+// its LDS read and its cursors whatever it moves: a copy in rounds of 2 KB took
+// 26.3, and 39 instead of 31 with its launch and wait where the source had just
+// been written and the register path, by nearness, takes 34. Rings of 8 and 16
+// KB (copies in 2 KB rounds): 16.7 and 13.2, 27.6 and 26.0. Beside the
 // GEMM it takes more from the GEMM than it gains (overlapped runs with rings of
 // 8 / 24 KB: 8192x8192x3584 461 -> 465 / 468, 16384x4096x3584 447 -> 447 / 449),
 // so the groups of an overlapped run keep the register path.
 template <int DT, bool SUM, bool WT>
 __device__ __forceinline__ void stream_ring(const ConsumeArgs& a) {
-    constexpr int kRing = 24 * 1024, kBatch = 2048, kSlot = SUM ? 2 * kBatch : kBatch, D = kRing / kSlot;
-    constexpr int kLoads = kSlot / 1024, kOps = kLoads + 2;     // per round: the loads, two stores
+    constexpr int kRing = 24 * 1024, kSlot = 4096, kBatch = SUM ? kSlot / 2 : kSlot, D = kRing / kSlot;
+    constexpr int kLoads = kSlot / 1024, kStores = kBatch / 1024, kOps = kLoads + kStores;   // per round
     static_assert((D - 1) * kOps <= 63, "the rounds in flight fit the vector memory counter");
     constexpr int kSc1Nt = 16 | 2;   // cache policy operand: sc1, nt
     __shared__ __attribute__((aligned(1024))) char ring[kRing];
@@ -384,12 +388,13 @@ __device__ __forceinline__ void stream_ring(const ConsumeArgs& a) {
         const int bytes = c.k >= a.nseg ? 0 : (int)(left < kBatch ? left : kBatch);
         char* const to = ring + slot * kSlot;
 #pragma unroll
-        for (int x = 0; x < kLoads / 2; ++x) {
+        for (int x = 0; x < (SUM ? 2 : 1); ++x) {
             const char* from = reinterpret_cast<const char*>(x == 0 ? a.src : a.peer) + c.from + at;
             const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)from, 0, bytes, kRsrcWord3);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)(to + x * kBatch), 16, lane * 16, 0, 0, kSc1Nt);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)(to + x * kBatch + 1024), 16, lane * 16 + 1024, 0,
-                                                     0, kSc1Nt);
+#pragma unroll
+            for (int y = 0; y < kStores; ++y)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)(to + x * kBatch + y * 1024), 16,
+                                                         lane * 16 + y * 1024, 0, 0, kSc1Nt);
         }
     };
     Cursor ahead{0, (int64_t)blockIdx.x, 0, 0, 0, 0};
@@ -408,28 +413,25 @@ __device__ __forceinline__ void stream_ring(const ConsumeArgs& a) {
         if (round < D) __builtin_amdgcn_s_waitcnt(wait_vm((D - 1) * kLoads));
         else __builtin_amdgcn_s_waitcnt(wait_vm((D - 1) * kOps));
         const uint32_t at = base + (uint32_t)(slot * kSlot);
-        u32x4_t x0, x1;
+        u32x4_t x[4];
         // (read in assembly: for a plain LDS read the compiler would wait for
         // every direct-to-LDS load in flight)
+        asm volatile("ds_read_b128 %0, %4\n ds_read_b128 %1, %4 offset:1024\n ds_read_b128 %2, %4 offset:2048\n"
+                     " ds_read_b128 %3, %4 offset:3072\n s_waitcnt lgkmcnt(0)"
+                     : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]) : "v"(at) : "memory");
         if constexpr (SUM) {
-            u32x4_t y0, y1;
-            asm volatile("ds_read_b128 %0, %4\n ds_read_b128 %1, %4 offset:1024\n ds_read_b128 %2, %4 offset:2048\n"
-                         " ds_read_b128 %3, %4 offset:3072\n s_waitcnt lgkmcnt(0)"
-                         : "=&v"(x0), "=&v"(x1), "=&v"(y0), "=&v"(y1) : "v"(at) : "memory");
-            x0 = add8<DT>(x0, y0);
-            x1 = add8<DT>(x1, y1);
-        } else {
-            asm volatile("ds_read_b128 %0, %2\n ds_read_b128 %1, %2 offset:1024\n s_waitcnt lgkmcnt(0)"
-                         : "=&v"(x0), "=&v"(x1) : "v"(at) : "memory");
+            x[0] = add8<DT>(x[0], x[2]);
+            x[1] = add8<DT>(x[1], x[3]);
         }
         // (through a resource that ends with the segment, not under a branch:
-        // both stores are issued in every round, as the wait above counts them)
+        // the stores are issued in every round, as the wait above counts them)
         const int64_t left = now.bytes - now.u * kBatch;
         const __amdgpu_buffer_rsrc_t d =
             __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char*>(a.dst) + now.to + now.u * kBatch, 0,
                                               (int)(left < kBatch ? left : kBatch), kRsrcWord3);
-        __builtin_amdgcn_raw_buffer_store_b128(x0, d, lane * 16, 0, WT ? 16 : 2);    // sc1 (see put16), or nt
-        __builtin_amdgcn_raw_buffer_store_b128(x1, d, lane * 16 + 1024, 0, WT ? 16 : 2);
+#pragma unroll
+        for (int y = 0; y < kStores; ++y)    // sc1 (see put16), or nt
+            __builtin_amdgcn_raw_buffer_store_b128(x[y], d, lane * 16 + y * 1024, 0, WT ? 16 : 2);
         asm volatile("" ::: "memory");
         load(ahead, slot);
         next(ahead);
@@ -584,7 +586,7 @@ hipError_t launch_consume(int dtype, int sync, const ConsumeArgs& a, int max_blo
     const bool sum = a.peer != nullptr;
     const int unroll = (full ? kUnrollFull : kUnrollBeside) * (sum ? 1 : 2);
     const int unroll8 = dtype == FO_BF16 ? (unroll < 2 ? unroll : 2) : (unroll < 4 ? unroll : 4);
-    const int64_t per_block = path == kPathRing ? 1024
+    const int64_t per_block = path == kPathRing ? (sum ? 1024 : 2048)
                               : path == kPathCoherent8 ? (int64_t)threads * 2 * unroll8 * 4
                               : path == kPathVec16 || path == kPathCoherent16 ? (int64_t)threads * unroll * 8
                                                                                : (int64_t)threads;

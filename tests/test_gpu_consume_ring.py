@@ -1,6 +1,6 @@
 """The consumer's LDS ring (one-wave workgroups, direct calls) on the GPU, at
-the edges of its batches (1024 elements) and of the rounds in flight per wave
-(6 of a sum, 12 of a copy), bit-exact against the oracle's sum."""
+the edges of its batches (1024 elements of a sum, 2048 of a copy) and of the 6
+rounds in flight per wave, bit-exact against the oracle's sum."""
 import numpy as np
 import pytest
 
@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("dtype", ["fp16", "bf16"])
 @pytest.mark.parametrize("length,blocks", [(n, b) for b in (1, 3, 256) for n in (
-    1, 8, 1023, 1024, 1025, 6 * 1024, 7 * 1024 + 9, 12 * 1024, 13 * 1024 + 511, 36 * 1024 + 5)] + [
+    1, 8, 1023, 1024, 1025, 2047, 2049, 6 * 1024, 7 * 1024 + 9, 12 * 1024, 13 * 1024 + 511, 36 * 1024 + 5)] + [
         (256 * 13 * 1024 + 7, 256)])
 def test_ring(length, blocks, dtype):
     torch = torch_mod()
