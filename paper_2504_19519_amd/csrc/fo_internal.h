@@ -19,7 +19,9 @@ namespace fo {
 
 // Tile computed by the workgroup at dispatch position p (fo_order in fo.h).
 // The GEMM kernel evaluates this on the device for its blockIdx, the planner
-// on the host for the reorder map, so both always agree.
+// on the host for the reorder map, so both always agree. In 32 bits: the caller
+// sees to 1 <= group_m <= max(tiles_m, 1) and num_xcds <= max(tiles, 1) (a plan
+// holds them so; block_band for a grid of blocks).
 FO_HD inline int32_t tile_of_position(int32_t p, int32_t tiles_m, int32_t tiles_n,
                                       int32_t order, int32_t group_m, int32_t num_xcds) {
     if (order == FO_ORDER_ROWMAJOR) return p;
@@ -41,6 +43,14 @@ FO_HD inline int32_t tile_of_position(int32_t p, int32_t tiles_m, int32_t tiles_
     const int32_t tm = first + r % rows;
     const int32_t tn = r / rows;
     return tm * tiles_n + tn;
+}
+
+// Band height, in blocks of block_m rows, of a launch whose workgroups compute
+// blocks and not the plan's tiles: the rows of the plan's band, rounded up, and
+// no taller than the grid of blocks_m block rows.
+inline int32_t block_band(int32_t group_m, int32_t tile_m, int32_t block_m, int32_t blocks_m) {
+    const int64_t band = ((int64_t)group_m * tile_m + block_m - 1) / block_m;
+    return band < blocks_m ? (int32_t)band : blocks_m < 1 ? 1 : blocks_m;
 }
 
 inline int dtype_bytes(int32_t) { return 2; }

@@ -544,7 +544,7 @@ hipError_t launch_gemm64(int dtype, GemmArgs a, int wave_width, bool share_cus, 
     a.blocks_m = (int)((a.M + bm - 1) / bm);
     a.blocks_n = (int)((a.N + bn - 1) / bn);
     // the same number of output rows per band as in the plan's order
-    a.block_band = bm == 128 ? (a.group_m + 1) / 2 : bm == 32 ? 2 * a.group_m : a.group_m;
+    a.block_band = block_band(a.group_m, 64, bm, a.blocks_m);
     const int64_t blocks = (int64_t)a.blocks_m * a.blocks_n;
     const bool pair = bm == 128 ? in_pairs(a, blocks, W, share_cus) : bn == 64 && share_cus && !a.trace;
     const int grid = (int)std::min<int64_t>(blocks, pair ? 2 * W : W);
@@ -577,7 +577,7 @@ bool gemm_in_parts(int tile_n, const GemmArgs& a, int wave_width) {
 hipError_t launch_gemm_parts(int dtype, int tile_n, GemmArgs a, int wave_width, bool share_cus, hipStream_t s) {
     a.blocks_m = (int)(a.M / 128);
     a.blocks_n = (int)(a.N / 128);
-    a.block_band = 2 * a.group_m;
+    a.block_band = block_band(a.group_m, 256, 128, a.blocks_m);
     a.num_dispensers = 1;
     const int64_t blocks = (int64_t)a.blocks_m * a.blocks_n, W = wave_width;
     const bool pair = in_pairs(a, blocks, W, share_cus);

@@ -188,8 +188,7 @@ fo_status build(fo_plan& p, const fo_problem& pr, const fo_grouping& g) {
 
     p.M = pr.M; p.N = pr.N; p.K = pr.K;
     p.dtype = pr.dtype; p.tile_m = pr.tile_m; p.tile_n = pr.tile_n;
-    p.order = pr.order; p.group_m = pr.order == FO_ORDER_ROWMAJOR ? 1 : pr.group_m;
-    p.num_xcds = pr.order == FO_ORDER_XCD ? pr.num_xcds : 1;
+    p.order = pr.order;
     p.num_cus = pr.num_cus; p.wg_per_cu = pr.wg_per_cu; p.reserved_cus = pr.reserved_cus;
     p.pattern = pr.pattern;
     p.num_dest = (pr.pattern == FO_PATTERN_SUBTILE || pr.pattern == FO_PATTERN_SUBTOKEN) ? pr.num_dest : 0;
@@ -198,6 +197,11 @@ fo_status build(fo_plan& p, const fo_problem& pr, const fo_grouping& g) {
     p.tiles = (int32_t)tiles64;
     p.W = (pr.num_cus - pr.reserved_cus) * pr.wg_per_cu;
     p.T = p.tiles ? (p.tiles + p.W - 1) / p.W : 0;
+    // One band over every tile row and one position per chiplet are the largest
+    // that make a difference: a larger value gives the same order, and kept as it
+    // is would overflow the order's 32-bit products.
+    p.group_m = pr.order == FO_ORDER_ROWMAJOR ? 1 : std::min(pr.group_m, std::max(p.tiles_m, 1));
+    p.num_xcds = pr.order == FO_ORDER_XCD ? std::min(pr.num_xcds, std::max(p.tiles, 1)) : 1;
 
     // dispatch order and the reorder map: slot = dispatch position
     p.order_tbl.resize(p.tiles);

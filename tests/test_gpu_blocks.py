@@ -92,3 +92,38 @@ def test_parts_of_larger_tiles(tile_n, widths, dtype, K):
                     assert_close_bits(got, oracle.gemm_ref(A, W, dtype).reshape(-1), dtype, "GEMM")
                 np.testing.assert_array_equal(got, plain[oracle.reorder_index(o)],
                                               err_msg=f"W={cus} {pattern} {'signalled' if counters is not None else ''}")
+
+
+@pytest.mark.parametrize("order", ["grouped", "xcd"])
+@pytest.mark.parametrize("tile,grid", [((64, 64), (4, 4)), ((64, 64), (4, 1)), ((64, 64), (4, 2)),
+                                       ((256, 128), (2, 3)), ((256, 256), (2, 1))])
+def test_bands_taller_than_the_output(tile, grid, order):
+    # "one band over everything" written as a large number (powers of two whose
+    # double, or whose product with the columns of a block grid, leaves 32 bits):
+    # the bits of any other order
+    torch = torch_mod()
+    K, (M, N) = 128, (tile[0] * grid[0], tile[1] * grid[1])
+    tiles = grid[0] * grid[1]
+    say(f"[gemm tall bands] {M}x{N}x{K} tile {tile} {order}")
+    rng = np.random.default_rng(tiles)
+    A = workloads.to_bits(rng.uniform(-1, 1, (M, K)), "bf16")
+    W = workloads.to_bits(rng.uniform(-1, 1, (N, K)) / np.sqrt(K), "bf16")
+    dA, dW = to_dev(A), to_dev(W)
+    plain = None
+    for group_m, xcds in [(1, 8), (1 << 28, 8), (1 << 29, 3), (1 << 30, 8), ((1 << 31) - 1, 8), (4, (1 << 31) - 20)]:
+        for cus in (4 * tiles, 2 * tiles, tiles, 2):      # 32x32, 64x32, whole tiles, 128x128 blocks
+            kw = dict(num_cus=cus, order=order, group_m=group_m, num_xcds=xcds, pattern="tile",
+                      sizes=[-(-tiles // cus)])
+            plan = fo.plan_groups(M, N, K, dtype="bf16", tile_m=tile[0], tile_n=tile[1], **kw)
+            o = oracle.make_plan(M, N, *tile, unit="waves", **kw)
+            dp = dev_plan(plan)
+            for counters in (None, zeros_u32(plan.num_counters)):
+                C = empty16(M * N, "bf16")
+                fo.gemm_signal_reorder(plan, dp, dA, dW, C, counters)
+                torch.cuda.synchronize()
+                got = from_dev(C)[:M * N]
+                if plain is None:
+                    plain = np.empty_like(got)
+                    plain[oracle.reorder_index(o)] = got
+                    assert_close_bits(plain, oracle.gemm_ref(A, W, "bf16").reshape(-1), "bf16", "GEMM")
+                np.testing.assert_array_equal(got, plain[oracle.reorder_index(o)], err_msg=f"{group_m} {xcds} {cus}")
