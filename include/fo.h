@@ -427,7 +427,12 @@ fo_status fo_reset_counters(uint32_t* counters, int32_t n, void* stream);
  * unspecified. The status word is sticky: the library only sets bits, the
  * caller clears it, so a timeout of one run stays visible after later runs
  * queued behind it. A gate that gives up because a later run's tag has
- * already arrived leaves the word as it is (that run is not delayed).
+ * already arrived leaves the word as it is (that run is not delayed). When the
+ * done wait gives up it takes the run's tag out of the gate word. Groups
+ * consumed together are not consumed at all once either wait has given up: the
+ * launch's workgroups that find another value than the run's tag in the gate
+ * word write neither dst nor out, so later work of gemm_stream (which goes on
+ * after the done wait) can use both.
  * A group's consumer is one wait kernel on the group's counter and one
  * streaming kernel that does what fo_consume_group does for each of the
  * group's plan segments (fo_plan_segments: 1, R or B of them). Every group

@@ -52,10 +52,13 @@ hipError_t launch_wait(const uint32_t* counter, uint32_t target, uint32_t* statu
 // Tags of the start handoff of an overlapped run: the run's reset kernel
 // writes its tag (bit 31 and 30 bits of the run's sequence number) into the
 // gate word once the counters are zero; the gate kernel on the other stream
-// waits for that tag. A gate that times out while the word holds an older
+// waits for that tag. A gate that times out while the word holds no later
 // run's tag replaces it by tag | kGateTimedOut, which the reset kernel, if it
-// runs later, turns into bit 0 of the status word; a gate that times out
-// after a later run's tag has arrived only raises the status bit.
+// runs later, leaves there and turns into bit 0 of the status word; a gate that
+// times out after a later run's tag has arrived only raises the status bit. The
+// done wait clears the word at the run's end, be it whole or timed out. So the
+// word holds a run's tag only while none of its waits has given up, and a launch
+// that may write what later work of the GEMM stream reads looks there first.
 constexpr uint32_t kGateTag = 0x80000000u;
 constexpr uint32_t kGateTimedOut = 0x40000000u;
 constexpr uint32_t kGateSeqMask = kGateTimedOut - 1;
@@ -88,12 +91,13 @@ __device__ __forceinline__ void count_done(uint32_t* done, uint32_t done_tag) {
 #endif
 // One wave that polls the done words until word k reaches done_tag plus
 // done_share(blocks, k) for every k (bounded like launch_wait), then clears the
-// gate word.
-hipError_t launch_done_wait(const uint32_t* done, uint32_t done_tag, int32_t blocks, uint32_t* gate, uint32_t* status,
-                            uint64_t timeout_ticks, hipStream_t s);
+// gate word (after a time-out if it holds the run's tag or its mark).
+hipError_t launch_done_wait(const uint32_t* done, uint32_t done_tag, int32_t blocks, uint32_t* gate, uint32_t tag,
+                            uint32_t* status, uint64_t timeout_ticks, hipStream_t s);
 hipError_t launch_gate(uint32_t* gate, uint32_t tag, uint32_t* status, uint64_t timeout_ticks, hipStream_t s);
 // One thread that counts as the only workgroup of a final launch, behind a
-// launch that does not count itself.
-hipError_t launch_mark_done(uint32_t* done, uint32_t done_tag, hipStream_t s);
+// launch that does not count itself; nothing unless the gate word holds the
+// run's tag.
+hipError_t launch_mark_done(uint32_t* done, uint32_t done_tag, const uint32_t* gate, uint32_t tag, hipStream_t s);
 
 }  // namespace fo

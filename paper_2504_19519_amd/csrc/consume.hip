@@ -95,9 +95,12 @@ __global__ __launch_bounds__(64) void wait_kernel(const uint32_t* counter, uint3
 // run's tag plus its share of the final launch's workgroups; the wave ends
 // when every lane's word has. Then the gate word is cleared: a captured run that
 // is replayed brings the same tag again and must not find it there. Bounded like
-// wait_kernel (a timed-out wait leaves the gate word alone).
+// wait_kernel. A timed-out wait clears the run's own tag or mark as well: from
+// then on the GEMM stream's later work runs, and what is left of this run on the
+// consumer stream must not take its gate for open.
 __global__ __launch_bounds__(64) void done_wait_kernel(const uint32_t* done, uint32_t done_tag, int32_t blocks,
-                                                       uint32_t* gate, uint32_t* status, uint64_t timeout_ticks) {
+                                                       uint32_t* gate, uint32_t tag, uint32_t* status,
+                                                       uint64_t timeout_ticks) {
     const int k = threadIdx.x;
     const bool mine = k < kDoneWords;
     const uint32_t target = done_tag + done_share(blocks, k);
@@ -106,7 +109,13 @@ __global__ __launch_bounds__(64) void done_wait_kernel(const uint32_t* done, uin
     while (!__all(!mine || __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= target)) {
         __builtin_amdgcn_s_sleep(8);
         if (wall_clock64() - t0 > timeout_ticks) {
-            if (k == 0 && status) __hip_atomic_fetch_or(status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (k != 0) return;
+            if (status) __hip_atomic_fetch_or(status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            uint32_t v = tag, mark = tag | kGateTimedOut;
+            __hip_atomic_compare_exchange_strong(gate, &v, 0u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_compare_exchange_strong(gate, &mark, 0u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
             return;
         }
     }
@@ -130,9 +139,8 @@ __global__ __launch_bounds__(64) void gate_kernel(uint32_t* gate, uint32_t tag, 
         __builtin_amdgcn_s_sleep(8);
         v = __hip_atomic_load(gate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (v != tag && wall_clock64() - t0 > timeout_ticks) {
-            // a later run's tag (sequence ahead of ours, modulo 2^30)
-            const bool later = (v & (kGateTag | kGateTimedOut)) == kGateTag &&
-                               (int32_t)(((v - tag) & kGateSeqMask) << 2) > 0;
+            // a later run's tag or mark (sequence ahead of ours, modulo 2^30)
+            const bool later = (v & kGateTag) && (int32_t)(((v - tag) & kGateSeqMask) << 2) > 0;
             if (later) {
                 if (status) __hip_atomic_fetch_or(status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 return;
@@ -149,8 +157,14 @@ __global__ __launch_bounds__(64) void gate_kernel(uint32_t* gate, uint32_t tag, 
 }
 
 // Counts a launch that ends with the kernel before this one on the stream.
-__global__ __launch_bounds__(64) void mark_done_kernel(uint32_t* done, uint32_t done_tag) {
-    if (threadIdx.x == 0) count_done(done, done_tag);
+__global__ __launch_bounds__(64) void mark_done_kernel(uint32_t* done, uint32_t done_tag, const uint32_t* gate,
+                                                       uint32_t tag) {
+    if (threadIdx.x != 0) return;
+    // (both words are read at once; one workgroup: word 0)
+    const uint32_t seen = __hip_atomic_load(gate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t v = __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (seen == tag && (v & 0xFFFF0000u) == done_tag)
+        __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Start of a streaming workgroup: one read of the counter (the wait kernel
@@ -544,9 +558,9 @@ hipError_t launch_wait(const uint32_t* counter, uint32_t target, uint32_t* statu
     return hipGetLastError();
 }
 
-hipError_t launch_done_wait(const uint32_t* done, uint32_t done_tag, int32_t blocks, uint32_t* gate, uint32_t* status,
-                            uint64_t timeout_ticks, hipStream_t s) {
-    hipLaunchKernelGGL(done_wait_kernel, dim3(1), dim3(64), 0, s, done, done_tag, blocks, gate, status,
+hipError_t launch_done_wait(const uint32_t* done, uint32_t done_tag, int32_t blocks, uint32_t* gate, uint32_t tag,
+                            uint32_t* status, uint64_t timeout_ticks, hipStream_t s) {
+    hipLaunchKernelGGL(done_wait_kernel, dim3(1), dim3(64), 0, s, done, done_tag, blocks, gate, tag, status,
                        timeout_ticks);
     return hipGetLastError();
 }
@@ -556,8 +570,8 @@ hipError_t launch_gate(uint32_t* gate, uint32_t tag, uint32_t* status, uint64_t 
     return hipGetLastError();
 }
 
-hipError_t launch_mark_done(uint32_t* done, uint32_t done_tag, hipStream_t s) {
-    hipLaunchKernelGGL(mark_done_kernel, dim3(1), dim3(64), 0, s, done, done_tag);
+hipError_t launch_mark_done(uint32_t* done, uint32_t done_tag, const uint32_t* gate, uint32_t tag, hipStream_t s) {
+    hipLaunchKernelGGL(mark_done_kernel, dim3(1), dim3(64), 0, s, done, done_tag, gate, tag);
     return hipGetLastError();
 }
 

@@ -29,10 +29,15 @@ struct PostArgs {
     const uint16_t* gemm_out;
     const uint16_t* peer;
     uint32_t bytes;
-    uint32_t* done;             // counts finished workgroups (see ConsumeArgs), or null
-    uint32_t done_tag;
     const int32_t* slot_group;
     const int32_t* group_first;
+    // Fused launches of an overlapped run: workgroups that find another value than
+    // gate_tag in the gate word (a wait of the run has given up) write nothing and
+    // are not counted. Null: no gate.
+    const uint32_t* gate;
+    uint32_t gate_tag;
+    uint32_t done_tag;
+    uint32_t* done;             // with a gate: counts finished workgroups (see ConsumeArgs), or null
 };
 
 // The kernel form of a launch.

@@ -132,10 +132,11 @@ __global__ void fill_u32_kernel(uint32_t* p, int32_t n, uint32_t v) {
 // Start of an overlapped run, one workgroup on the GEMM stream: zero the
 // group and position counters (n words), set the kDoneWords done words to
 // the run's done tag with a count of zero, make both visible device-wide, then
-// exchange the gate word for the run's tag (the start handoff that the gate
+// put the run's tag into the gate word (the start handoff that the gate
 // kernel on the consumer stream waits for). If a gate of this run timed out
-// before, the word holds the tag's timed-out mark: the status word then gets
-// bit 0 (the status word is never cleared here: its bits are sticky).
+// before, the word holds the tag's timed-out mark: it stays, so that what follows
+// the gate on the consumer stream does not take it for open, and the status word
+// gets bit 0 (it is never cleared here: its bits are sticky).
 // group_first (device plan table) non-null: the launch follows the run's GEMM,
 // every group is complete, and the `groups` counters get their targets.
 __global__ __launch_bounds__(256) void reset_run_kernel(uint32_t* counters, int32_t n, const int32_t* group_first,
@@ -147,7 +148,11 @@ __global__ __launch_bounds__(256) void reset_run_kernel(uint32_t* counters, int3
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     __syncthreads();
     if (threadIdx.x == 0) {
-        const uint32_t old = __hip_atomic_exchange(gate, tag, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        uint32_t old = 0u;      // what the run before has left, unless a wait gave up
+        while (old != (tag | kGateTimedOut) &&
+               !__hip_atomic_compare_exchange_strong(gate, &old, tag, __ATOMIC_RELEASE, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT)) {
+        }
         if (old == (tag | kGateTimedOut) && status)
             __hip_atomic_fetch_or(status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -569,16 +574,18 @@ fo_status fo_run_overlapped(const fo_plan* plan, const void* dev_plan, const voi
         // words), by a kernel of one thread behind it
         if ((st = hand_over()) != FO_OK) return st;
         const bool mark = fo::post_form(post, true).blocks > 512;
+        post.gate = gate;
+        post.gate_tag = tag;
         if (!mark) {
             post.done = done;
             post.done_tag = done_tag;
         }
         if ((e = fo::launch_post(plan->dtype, post, true, s2)) != hipSuccess)
             return fo::hip_fail("post-reorder launch", e);
-        if (mark && (e = fo::launch_mark_done(done, done_tag, s2)) != hipSuccess)
+        if (mark && (e = fo::launch_mark_done(done, done_tag, gate, tag, s2)) != hipSuccess)
             return fo::hip_fail("mark kernel launch", e);
         const int blocks = mark ? 1 : (int)fo::post_form(post, true).blocks;
-        e = fo::launch_done_wait(done, done_tag, blocks, gate, status_word, ticks, s1);
+        e = fo::launch_done_wait(done, done_tag, blocks, gate, tag, status_word, ticks, s1);
         return e == hipSuccess ? FO_OK : fo::hip_fail("wait kernel launch", e);
     }
     // One consumer launch per group (more if a group has more pieces than a
@@ -630,7 +637,7 @@ fo_status fo_run_overlapped(const fo_plan* plan, const void* dev_plan, const voi
     // grid only through this run's final consumer (a late consumer of an
     // earlier run finds another tag in them and does not count)
     if (final_blocks > 0 &&
-        (e = fo::launch_done_wait(done, done_tag, final_blocks, gate, status_word, ticks, s1)) != hipSuccess)
+        (e = fo::launch_done_wait(done, done_tag, final_blocks, gate, tag, status_word, ticks, s1)) != hipSuccess)
         return fo::hip_fail("wait kernel launch", e);
     if (out) return fo_post_reorder(plan, dev_plan, dst, out, bias, gamma, eps, do_rmsnorm, s1);
     return FO_OK;

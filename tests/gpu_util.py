@@ -2,6 +2,7 @@
 value tolerance, and a runner for one whole path through the C ABI."""
 from __future__ import annotations
 
+import itertools
 import math
 import sys
 
@@ -91,3 +92,30 @@ def plan_for(w: workloads.Workload, inp: workloads.Inputs, *, num_cus=256, sizes
                          sigma=inp.sigma, bucket=inp.bucket,
                          sizes=sizes, unit=unit)
     return p, o
+
+
+def streams_apart(candidates: int = 6):
+    """Two streams on different hardware queues. (HIP maps streams onto a few
+    queues; kernels of streams that share one run one after another, and a held
+    stream then holds the other one too.)"""
+    torch = torch_mod()
+
+    def apart(a, b):
+        for held, free in ((a, b), (b, a)):
+            torch.cuda.synchronize()
+            eh, ef = torch.cuda.Event(), torch.cuda.Event()
+            with torch.cuda.stream(held):
+                torch.cuda._sleep(20_000_000)
+            eh.record(held)
+            ef.record(free)
+            ef.synchronize()
+            if eh.query():
+                return False
+        torch.cuda.synchronize()
+        return True
+
+    streams = [torch.cuda.Stream() for _ in range(candidates)]
+    for pair in itertools.combinations(streams, 2):
+        if apart(*pair):
+            return pair
+    raise AssertionError(f"no two of {candidates} streams run side by side (GPU_MAX_HW_QUEUES of 1?)")
