@@ -403,7 +403,10 @@ fo_status fo_reset_counters(uint32_t* counters, int32_t n, void* stream);
  * its consumer, both estimated from the sizes and W) whose options leave the
  * consumer grid and the sync modes at their built-in defaults consumes all
  * groups in one launch behind the GEMM, fused with the post-reorder (the same
- * values in dst and out, the counters as below):
+ * values in dst and out, the counters as below). Its gate waits for the whole
+ * GEMM besides the work queued ahead of it, so that a run whose poll_timeout_us
+ * is below 10 ms or below a hundred times the GEMM's estimate has a launch per
+ * group.
  *   gemm_stream: GEMM -> reset kernel (counters at their targets) -> done wait
  *   comm_stream: gate kernel -> consumer + post-reorder
  *                [-> mark kernel, when its workgroups are too many to be counted]

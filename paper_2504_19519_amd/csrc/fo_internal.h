@@ -101,3 +101,34 @@ struct fo_plan {
     fo_dev_layout layout;
     std::vector<int32_t> image;         // device image (layout.words)
 };
+
+namespace fo {
+
+// Whether the groups of an overlapped run are consumed together, after the
+// GEMM. On one device a consumer beside the GEMM takes from the GEMM about what
+// it saves behind it, and every group costs a wait kernel and a launch, while
+// consumed together the groups share one pass with the post-reorder. Measured
+// (us per run, a launch per group / together):
+//   256x256x256     4 groups  49 / 19     4096x7168x2048  2 groups  146 / 128
+//   1216x2880x1984  4 groups  60 / 32     8192x4096x4096  2 groups  253 / 248
+//   4096x4096x4096  2 groups 168 / 136    8192x8192x1024  3 groups  290 / 207
+//   16384x8192x2048 4 groups 611 / 591    8192x8192x3584  3 groups  456 / 447
+//   16384x4096x3584 4 groups 442 / 445    32768x4096x3584 4 groups  869 / 878
+//   8192x8192x7168  4 groups 747 / 763
+// A launch per group pays once the GEMM (at the 5.5 TFLOP/s that a compute unit
+// reaches) lasts 300 us and three times as long as the consumer alone (at 5.1
+// TB/s): below that the groups after the first still run when the GEMM ends. (Two
+// of the table's shapes have the same estimates and differ the other way,
+// 8192x8192x3584 by 2 % and 16384x4096x3584 by 1 %; no line in the sizes parts
+// them.)
+// Consumed together, one wait (limit_us) holds the consumer stream for all of the
+// GEMM, where a launch per group waits for a group at a time. A caller's limit that
+// was set for the groups must not expire on that: it has to exceed the estimate a
+// hundredfold, and 10 ms, which a device shared with other work does not use up.
+inline bool consumed_together(const fo_plan& p, bool sum, int64_t limit_us) {
+    const double gemm_us = 2.0 * (double)p.M * (double)p.N * (double)p.K / ((p.W > 1 ? p.W : 1) * 5.5e6);
+    const double consume_us = 2.0 * (double)p.M * (double)p.N * (sum ? 3 : 2) / 5.1e6;
+    return (gemm_us < 300.0 || gemm_us < 3.0 * consume_us) && (double)limit_us >= 100.0 * gemm_us && limit_us >= 10000;
+}
+
+}  // namespace fo

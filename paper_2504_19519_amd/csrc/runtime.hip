@@ -266,26 +266,6 @@ bool plain_consumer(const fo_options& o) {
            o.sync_producer == FO_SYNC_COHERENT && o.sync_consumer == FO_SYNC_COHERENT;
 }
 
-// Whether the groups of an overlapped run are consumed together, after the
-// GEMM. On one device a consumer beside the GEMM takes from the GEMM about what
-// it saves behind it, and every group costs a wait kernel and a launch, while
-// consumed together the groups share one pass with the post-reorder. Measured
-// (us per run, a launch per group / together):
-//   256x256x256     4 groups  49 / 19     4096x7168x2048  2 groups  146 / 128
-//   1216x2880x1984  4 groups  60 / 32     8192x4096x4096  2 groups  253 / 248
-//   4096x4096x4096  2 groups 168 / 136    8192x8192x1024  3 groups  290 / 207
-//   16384x8192x2048 4 groups 611 / 591    8192x8192x3584  3 groups  456 / 447
-//   16384x4096x3584 4 groups 442 / 445    32768x4096x3584 4 groups  869 / 878
-//   8192x8192x7168  4 groups 747 / 763
-// A launch per group pays once the GEMM (at the 5.5 TFLOP/s that a compute unit
-// reaches) lasts 300 us and three times as long as the consumer alone (at 5.1
-// TB/s): below that the groups after the first still run when the GEMM ends.
-bool short_run(const fo_plan& p, bool sum) {
-    const double gemm_us = 2.0 * (double)p.M * (double)p.N * (double)p.K / (std::max(p.W, 1) * 5.5e6);
-    const double consume_us = 2.0 * (double)p.M * (double)p.N * (sum ? 3 : 2) / 5.1e6;
-    return gemm_us < 300.0 || gemm_us < 3.0 * consume_us;
-}
-
 // Whether [p, p + bytes) and [q, q + bytes) share a byte.
 bool overlap(const void* p, const void* q, int64_t bytes) {
     const uintptr_t x = reinterpret_cast<uintptr_t>(p), y = reinterpret_cast<uintptr_t>(q);
@@ -535,7 +515,8 @@ fo_status fo_run_overlapped(const fo_plan* plan, const void* dev_plan, const voi
     fo::PostArgs post{};
     const int64_t bytes = plan->M * plan->N * 2;
     bool fused = out && C_out && o.consumer_limit == 0 && bytes > 0 && fo::aligned16(peer) &&
-                 (!overlap || (dev_plan && fo::plain_consumer(o) && fo::short_run(*plan, peer != nullptr)));
+                 (!overlap || (dev_plan && fo::plain_consumer(o) &&
+                              fo::consumed_together(*plan, peer != nullptr, o.poll_timeout_us)));
     if (fused)
         fused = fo::post_args(plan, dev_plan, dst, out, bias, gamma, eps, do_rmsnorm, &post) == FO_OK &&
                 fo::post_fusable(post) && !fo::overlap(out, C_out, bytes) &&

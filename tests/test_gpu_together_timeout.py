@@ -73,3 +73,31 @@ def test_nothing_is_written_after_a_wait_gave_up(held, M, norm, pair):
             assert torch.equal(x, y), f"round {k}: {what}"
         assert counters[:plan.P].tolist() == list(plan.targets)
         assert int(counters[plan.P + fo.DISPENSER_WORDS]) == 0, "gate word"
+
+
+def test_the_next_run_is_whole(pair):
+    # the consumer stream is held; a run with a short limit and one with the normal
+    # limit are queued back to back on the same buffers. The first gives up and its
+    # late launch finds the second run's tag; the second waits for its own.
+    torch = torch_mod()
+    M, N, K = 512, 512, 128
+    s1, s2 = pair
+    say(f"[together, timed out back-to-back] {M}x{N}x{K}")
+    plan = fo.plan_groups(M, N, K, dtype="fp16", tile_m=64, tile_n=64, pattern="tile", sizes=[16, 16, 32], unit="tiles")
+    dp = dev_plan(plan)
+    As = [torch.randn(M * K, device="cuda").half() for _ in range(2)]
+    W, peer = (torch.randn(n, device="cuda").half() for n in (N * K, M * N))
+    C, dst, first, out, C2, dst2, out2 = (empty16(M * N, "fp16") for _ in range(7))
+    counters, status = zeros_u32(plan.num_counters), zeros_u32(1)
+    fo.run_overlapped(plan, dp, As[1], W, C2, peer, dst2, out2)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s2):
+        torch.cuda._sleep(HOLD)
+    for A, o, opts in ((As[0], first, LIMIT), (As[1], out, None)):
+        fo.run_overlapped(plan, dp, A, W, C, peer, dst, o, counters=counters, status_word=status, gemm_stream=s1,
+                          comm_stream=s2, opts=opts)
+    torch.cuda.synchronize()
+    assert int(status.cpu()[0]) & 1 == 1
+    assert bool((first == 0x7E00).all())
+    for what, x, y in (("C", C, C2), ("dst", dst, dst2), ("out", out, out2)):
+        assert torch.equal(x, y), what
