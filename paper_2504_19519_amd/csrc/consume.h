@@ -39,7 +39,7 @@ struct ConsumeArgs {
 // in flight per thread); otherwise it runs beside the GEMM and keeps its
 // registers within what a SIMD running two GEMM waves has left. ring: a launch
 // of one-wave workgroups may stream through LDS (coherent mode, 16-byte aligned
-// buffers).
+// buffers, one segment, not counted).
 // *blocks (if non-null) receives the streaming kernel's grid size.
 hipError_t launch_consume(int dtype, int sync, const ConsumeArgs& a, int max_blocks, int threads, bool full, bool ring,
                           hipStream_t s, int* blocks = nullptr);

@@ -338,7 +338,7 @@ __device__ __forceinline__ void stream_coherent16(const uint16_t* __restrict__ s
     }
 }
 
-// All segments of a launch of one-wave workgroups, through a ring in LDS
+// The one segment of a launch of one-wave workgroups, through a ring in LDS
 // (COHERENT; 16-byte aligned buffers of any size). Such a launch has one wave
 // per compute unit, so what it streams is what that wave keeps in flight over a
 // memory latency; the registers that a GEMM wave leaves it hold 4 KB, the LDS
@@ -348,79 +348,57 @@ __device__ __forceinline__ void stream_coherent16(const uint16_t* __restrict__ s
 // on in its place. A batch past the wave's last one is loaded through an empty
 // resource, so that every round has the same number of operations in flight.
 // Alone, 256 workgroups (us, register path -> ring; floor at 5.1 TB/s): sum of
-// 8388613 fp16 23.7 -> 12.5 (9.9) with its wait kernel, copy of 29360128 38.9 ->
-// 20.2 (23.0; part of it is in the memory-side cache). A round costs its wait,
-// its LDS read and its cursors whatever it moves: a copy in rounds of 2 KB took
-// 26.3, and 39 instead of 31 with its launch and wait where the source had just
-// been written and the register path, by nearness, takes 34. Rings of 8 and 16
-// KB (copies in 2 KB rounds): 16.7 and 13.2, 27.6 and 26.0. Beside the
-// GEMM it takes more from the GEMM than it gains (overlapped runs with rings of
-// 8 / 24 KB: 8192x8192x3584 461 -> 465 / 468, 16384x4096x3584 447 -> 447 / 449),
-// so the groups of an overlapped run keep the register path.
-template <int DT, bool SUM, bool WT>
-__device__ __forceinline__ void stream_ring(const ConsumeArgs& a) {
+// 8388613 fp16 23.7 -> 11.7 (9.9) with its wait kernel. Copy of 29360128, whose 117
+// MB stay in the memory-side cache from call to call, 38.9 -> 19.6 (23.0 from
+// memory); with its launch and wait, on a source that has just been written and
+// buffers seen for the first time, 34 -> 31. A round costs its wait, its LDS read
+// and its addresses whatever it moves: a copy in rounds of 2 KB took 26.3 and, on
+// first sight, 39. Rings of 8 and 16 KB (copies in 2 KB rounds): 16.7 and 13.2,
+// 27.6 and 26.0.
+// Beside the GEMM it slows the GEMM more than the register path does. A caller that
+// consumes each group by a call of its own gains all the same, by what the groups
+// then take behind it (us per step, register path -> ring: 8192x8192x3584 in three
+// groups 473 -> 446, in four 432 -> 420; 4096x4096x4096 166 -> 157; plans of 64x64
+// tiles 47.5 -> 45.4 and 140 -> 135). fo_run_overlapped's groups do not: their last
+// one has a launch that fills the device anyway (rings of 8 / 24 KB: 8192x8192x3584
+// 461 -> 465 / 468, 16384x4096x3584 447 -> 447 / 449). They keep the register path.
+template <int DT, bool SUM>
+__device__ __forceinline__ void stream_ring(const uint16_t* src, const uint16_t* peer, uint16_t* dst, int64_t len) {
     constexpr int kRing = 24 * 1024, kSlot = 4096, kBatch = SUM ? kSlot / 2 : kSlot, D = kRing / kSlot;
     constexpr int kLoads = kSlot / 1024, kStores = kBatch / 1024, kOps = kLoads + kStores;   // per round
     static_assert((D - 1) * kOps <= 63, "the rounds in flight fit the vector memory counter");
-    constexpr int kSc1Nt = 16 | 2;   // cache policy operand: sc1, nt
+    constexpr int kNt = 2, kSc1Nt = 16 | 2;   // cache policy operands
     __shared__ __attribute__((aligned(1024))) char ring[kRing];
     typedef __attribute__((address_space(3))) char lds_char_t;
     typedef __attribute__((address_space(3))) void lds_void_t;
     const int lane = threadIdx.x;
-    const int64_t grid = gridDim.x;
-    // This wave's batches: every grid-th of the segments' batches in a row. A
-    // cursor holds its segment's bounds in scalar registers; the segment table
-    // is only read again when a segment ends.
-    struct Cursor {
-        int k;
-        int64_t u, n;              // batch u of the segment's n
-        int64_t from, to, bytes;   // byte offsets of the segment, its whole chunks
+    // This wave's batches: every grid-th of the segment's.
+    const int64_t bytes = (len >> 3) * 16, batches = (bytes + kBatch - 1) / kBatch;
+    // what batch u holds (past the last one: nothing)
+    auto held = [&](int64_t u) -> int {
+        const int64_t left = bytes - u * kBatch;
+        return u >= batches ? 0 : (int)(left < kBatch ? left : kBatch);
     };
-    auto enter = [&](Cursor& c) {
-        while (c.k < a.nseg) {
-            const ConsumeSegment g = a.seg[c.k];
-            c.from = g.src_off * 2;
-            c.to = g.dst_off * 2;
-            c.bytes = (g.len >> 3) * 16;
-            c.n = (c.bytes + kBatch - 1) / kBatch;
-            if (c.u < c.n) return;
-            c.u -= c.n;
-            ++c.k;
-        }
-        c.u = c.bytes = c.from = 0;    // past the last one: nothing to load
-    };
-    auto next = [&](Cursor& c) {
-        c.u += grid;
-        if (c.u >= c.n && c.k < a.nseg) {
-            c.u -= c.n;
-            ++c.k;
-            enter(c);
-        }
-    };
-    auto load = [&](const Cursor& c, int slot) {
-        const int64_t at = c.u * kBatch, left = c.bytes - at;
-        const int bytes = c.k >= a.nseg ? 0 : (int)(left < kBatch ? left : kBatch);
+    auto load = [&](int64_t u, int slot) {
         char* const to = ring + slot * kSlot;
+        const int n = held(u);
+        const int64_t at = n > 0 ? u * kBatch : 0;
 #pragma unroll
         for (int x = 0; x < (SUM ? 2 : 1); ++x) {
-            const char* from = reinterpret_cast<const char*>(x == 0 ? a.src : a.peer) + c.from + at;
-            const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)from, 0, bytes, kRsrcWord3);
+            const char* from = reinterpret_cast<const char*>(x == 0 ? src : peer) + at;
+            const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)from, 0, n, kRsrcWord3);
 #pragma unroll
             for (int y = 0; y < kStores; ++y)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)(to + x * kBatch + y * 1024), 16,
                                                          lane * 16 + y * 1024, 0, 0, kSc1Nt);
         }
     };
-    Cursor ahead{0, (int64_t)blockIdx.x, 0, 0, 0, 0};
-    enter(ahead);
-    Cursor now = ahead;
-    for (int d = 0; d < D; ++d) {
-        load(ahead, d);
-        next(ahead);
-    }
+    const int64_t grid = gridDim.x;
+    int64_t ahead = blockIdx.x;
+    for (int d = 0; d < D; ++d, ahead += grid) load(ahead, d);
     const uint32_t base = (uint32_t)(uintptr_t)(lds_char_t*)ring + (uint32_t)lane * 16u;
-    int slot = 0;
-    for (int round = 0; now.k < a.nseg; ++round) {
+    int slot = 0, round = 0;
+    for (int64_t u = blockIdx.x; u < batches; u += grid, ahead += grid, ++round) {
         // the loads of this slot are the oldest ones: younger are the loads of
         // D - 1 rounds and, once the first D rounds are over, their stores
         asm volatile("" ::: "memory");
@@ -439,29 +417,20 @@ __device__ __forceinline__ void stream_ring(const ConsumeArgs& a) {
         }
         // (through a resource that ends with the segment, not under a branch:
         // the stores are issued in every round, as the wait above counts them)
-        const int64_t left = now.bytes - now.u * kBatch;
-        const __amdgpu_buffer_rsrc_t d =
-            __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char*>(a.dst) + now.to + now.u * kBatch, 0,
-                                              (int)(left < kBatch ? left : kBatch), kRsrcWord3);
+        const __amdgpu_buffer_rsrc_t d = __builtin_amdgcn_make_buffer_rsrc(
+            reinterpret_cast<char*>(dst) + u * kBatch, 0, held(u), kRsrcWord3);
 #pragma unroll
-        for (int y = 0; y < kStores; ++y)    // sc1 (see put16), or nt
-            __builtin_amdgcn_raw_buffer_store_b128(x[y], d, lane * 16 + y * 1024, 0, WT ? 16 : 2);
+        for (int y = 0; y < kStores; ++y)
+            __builtin_amdgcn_raw_buffer_store_b128(x[y], d, lane * 16 + y * 1024, 0, kNt);
         asm volatile("" ::: "memory");
         load(ahead, slot);
-        next(ahead);
-        next(now);
         slot = slot + 1 == D ? 0 : slot + 1;
     }
-    // ragged tails (< 8 elements): an acquire, then plain 2-byte loads
-    if (blockIdx.x == 0) {
+    // ragged tail (< 8 elements): an acquire, then plain 2-byte loads
+    if (blockIdx.x == 0 && lane < (len & 7)) {
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        for (int k = 0; k < a.nseg; ++k) {
-            const ConsumeSegment g = a.seg[k];
-            if (lane >= (g.len & 7)) continue;
-            const int64_t e = (g.len >> 3 << 3) + lane;
-            const uint16_t x = a.src[g.src_off + e];
-            put2<WT>(a.dst + g.dst_off + e, SUM ? add1<DT>(x, a.peer[g.src_off + e]) : x);
-        }
+        const int64_t e = (len >> 3 << 3) + lane;
+        put2<false>(dst + e, SUM ? add1<DT>(src[e], peer[e]) : src[e]);
     }
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);    // no load may still be writing LDS
 }
@@ -490,9 +459,7 @@ enum { kPathVec16 = 0, kPathCoherent8 = 1, kPathElem = 2, kPathCoherent16 = 3, k
 template <int DT, bool SUM, int SYNC, int PATH, int U, bool WT>
 __global__ __launch_bounds__(kMaxThreads) void consume_kernel(const ConsumeArgs a) {
     const bool go = !a.counter || check_counter<SYNC>(a.counter, a.target, a.status);
-    if constexpr (PATH == kPathRing) {
-        if (go) stream_ring<DT, SUM, WT>(a);
-    } else if (go) {
+    if (go) {
         uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;   // < grid size: fits 32 bits
         for (int k = 0; k < a.nseg; ++k) {
             const ConsumeSegment g = a.seg[k];
@@ -512,6 +479,14 @@ __global__ __launch_bounds__(kMaxThreads) void consume_kernel(const ConsumeArgs 
     }
 }
 
+// The ring's launch: one segment, not counted.
+template <int DT, bool SUM>
+__global__ __launch_bounds__(64) void ring_consume_kernel(const ConsumeArgs a) {
+    if (a.counter && !check_counter<FO_SYNC_COHERENT>(a.counter, a.target, a.status)) return;
+    const ConsumeSegment g = a.seg[0];
+    stream_ring<DT, SUM>(a.src + g.src_off, SUM ? a.peer + g.src_off : nullptr, a.dst + g.dst_off, g.len);
+}
+
 // Unroll of the 8-byte coherent path (outputs past a 31-bit byte range): at
 // most 4 x 2 units per thread in flight, 2 x 2 for bf16, whose sums need
 // more registers (4 x 2 bf16 units took ~87 registers, more than a SIMD
@@ -521,9 +496,7 @@ constexpr int kUnit8Unroll = DT == FO_BF16 ? (U < 2 ? U : 2) : (U < 4 ? U : 4);
 
 template <int DT, bool SUM, int U, bool WT>
 void launch_variant(int sync, int path, dim3 g, dim3 b, hipStream_t s, const ConsumeArgs& a) {
-    if (path == kPathRing)
-        hipLaunchKernelGGL((consume_kernel<DT, SUM, FO_SYNC_COHERENT, kPathRing, 1, WT>), g, b, 0, s, a);
-    else if (path == kPathCoherent16)
+    if (path == kPathCoherent16)
         hipLaunchKernelGGL((consume_kernel<DT, SUM, FO_SYNC_COHERENT, kPathCoherent16, U, WT>), g, b, 0, s, a);
     else if (path == kPathCoherent8)   // bf16 sums: fewer 8-byte units in flight (the budget of registers)
         hipLaunchKernelGGL((consume_kernel<DT, SUM, FO_SYNC_COHERENT, kPathCoherent8, kUnit8Unroll<DT, U>, WT>), g,
@@ -544,7 +517,8 @@ template <int DT, bool SUM>
 void launch_unroll(bool full, int sync, int path, dim3 g, dim3 b, hipStream_t s, const ConsumeArgs& a) {
     constexpr int kFull = SUM ? kUnrollFull : 2 * kUnrollFull;
     constexpr int kBeside = SUM ? kUnrollBeside : 2 * kUnrollBeside;
-    if (a.done && full) launch_variant<DT, SUM, kFull, true>(sync, path, g, b, s, a);
+    if (path == kPathRing) hipLaunchKernelGGL((ring_consume_kernel<DT, SUM>), g, b, 0, s, a);
+    else if (a.done && full) launch_variant<DT, SUM, kFull, true>(sync, path, g, b, s, a);
     else if (a.done) launch_variant<DT, SUM, kBeside, true>(sync, path, g, b, s, a);
     else if (full) launch_variant<DT, SUM, kFull, false>(sync, path, g, b, s, a);
     else launch_variant<DT, SUM, kBeside, false>(sync, path, g, b, s, a);
@@ -592,7 +566,7 @@ hipError_t launch_consume(int dtype, int sync, const ConsumeArgs& a, int max_blo
     // the 16-byte coherent path addresses a segment with 32-bit byte offsets
     const bool fits32 = longest * 2 <= 0x7FFFFFFF;
     const int path = sync == FO_SYNC_COHERENT
-                         ? (vec16 && threads == 64 && ring ? kPathRing
+                         ? (vec16 && ring && threads == 64 && a.nseg == 1 && !a.done ? kPathRing
                             : vec16 && fits32 ? kPathCoherent16 : vec8 ? kPathCoherent8 : kPathElem)
                          : (vec16 ? kPathVec16 : kPathElem);
     // elements one workgroup moves per unrolled round (the unrolls of
@@ -610,8 +584,7 @@ hipError_t launch_consume(int dtype, int sync, const ConsumeArgs& a, int max_blo
     const dim3 g((unsigned)blocks), b((unsigned)threads);
     if (launched_blocks) *launched_blocks = (int)blocks;
     if (a.counter) {
-        hipLaunchKernelGGL(wait_kernel, dim3(1), dim3(64), 0, s, a.counter, a.target, a.status, a.timeout_ticks);
-        const hipError_t e = hipGetLastError();
+        const hipError_t e = launch_wait(a.counter, a.target, a.status, a.timeout_ticks, s);
         if (e != hipSuccess) return e;
     }
     if (dtype == FO_FP16) {
