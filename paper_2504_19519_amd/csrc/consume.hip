@@ -17,11 +17,13 @@
 // workgroups write nothing and bit 0 of the status word is raised, so a
 // missing signal can never hang the device.
 //
-// A consumer workgroup holds 4 bytes of LDS (24 KB with a ring) and at most 57
-// registers per lane, so it fits beside a GEMM workgroup on the same compute
-// unit (the GEMM kernels leave at least 64 registers per SIMD lane and 26 KB of
-// LDS free): polling consumers share compute units with the GEMM instead of
-// taking them away from it.
+// A consumer workgroup holds 4 bytes of LDS and at most 57 registers per lane, so it
+// fits beside the GEMM's workgroups on a compute unit, be it one or a pair of blocks
+// (they leave at least 64 registers per SIMD lane and 11 KB of LDS): consumers share
+// compute units with the GEMM instead of taking them away from it. The ring of a
+// direct call, 24 KB of LDS, fits beside one GEMM workgroup (26 KB free). Beside a
+// pair it does not, and its workgroups start as blocks retire: pairs make one round,
+// and a step is still shorter than with the register path (stream_ring).
 #include <hip/hip_runtime.h>
 
 #include "consume.h"

@@ -1,9 +1,10 @@
-"""A consumer workgroup must fit on a compute unit beside a GEMM workgroup.
+"""A consumer workgroup must fit on a compute unit beside the GEMM's workgroups.
 
-The consumer kernels poll and stream while the persistent GEMM holds one
-workgroup per compute unit; if a consumer workgroup did not fit beside it, it
-would take the compute unit away from the GEMM for as long as it waits. The
-budget is checked on the compiler's resource report that the build writes
+The consumer kernels poll and stream while the GEMM holds one workgroup per
+compute unit, or two (the block kernels that are launched in pairs); if a
+consumer workgroup did not fit beside them, it would wait for one of them to
+retire. The ring consumer of direct calls, whose LDS a pair does not leave, fits
+beside one. The budget is checked on the compiler's resource report that the build writes
 (gfx950: 512 registers per SIMD lane, allocated in blocks of 8; 160 KiB of
 LDS per compute unit; a consumer workgroup has one wave per SIMD).
 """
@@ -39,9 +40,12 @@ def test_consumer_fits_beside_every_gemm_kernel():
     gemm = {k: v for k, v in u.items()
             if "gemm_signal_kernel" in k or "gemm_w4_kernel" in k or "gemm_w4n_kernel" in k}
     cons = {k: v for k, v in u.items() if "consume_kernel" in k}
-    assert len(gemm) >= 6 and len(cons) >= 8
+    ring = {k: v for k, v in cons.items() if "ring_consume_kernel" in k}
+    assert len(gemm) >= 6 and len(cons) >= 8 and len(ring) == 4
     c_regs = max(_regs(v) for v in cons.values())
-    c_lds = max(v["lds"] for v in cons.values())
+    ring_lds = max(v["lds"] for v in ring.values())
+    c_lds = max(v["lds"] for k, v in cons.items() if k not in ring)
+    pairs = 0
     for name, v in gemm.items():
         # register spills may only go to other registers (no scratch memory)
         assert v.get("scratch", 0) == 0, name
@@ -53,6 +57,14 @@ def test_consumer_fits_beside_every_gemm_kernel():
             m = re.search(r"gemm_signal_kernelILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)E", name)
             assert m, name
             per_simd = (int(m.group(4)) * int(m.group(5)) + 3) // 4
+            # the block kernels that are launched two to a compute unit: 128x128
+            # with two stages, 64x64 with four
+            if (m.group(2), m.group(3), m.group(6)) in (("128", "128", "2"), ("64", "64", "4")):
+                pairs += 1
+                regs, lds = 2 * per_simd * _regs(v), 2 * v["lds"]
+                assert regs + c_regs <= 512, (name, regs, c_regs)
+                assert lds + c_lds <= 160 * 1024, (name, lds, c_lds)
         regs = per_simd * _regs(v)
         assert regs + c_regs <= 512, (name, regs, c_regs)
-        assert v["lds"] + c_lds <= 160 * 1024, (name, v["lds"], c_lds)
+        assert v["lds"] + max(c_lds, ring_lds) <= 160 * 1024, (name, v["lds"], c_lds, ring_lds)
+    assert pairs >= 4          # both dtypes of both
