@@ -9,6 +9,10 @@ RMSNorm runs), every counter ends at its group's tile count, and the GEMM
 values match the exact product (every output, at the reduced and at the full
 sizes). Destination buffers are filled with NaN before each
 run, so a consumer that read a group early would leave NaNs behind.
+
+Short runs with default options consume their groups together, behind an
+unsignalled GEMM. Where a test is about signals, counts or the launch per group,
+it runs with options that keep that launch as well (PER_GROUP).
 """
 import numpy as np
 import pytest
@@ -39,6 +43,11 @@ class Dev:
         self.bias = to_dev(inp.bias) if inp.bias is not None else None
         self.gamma = to_dev(inp.gamma) if inp.gamma is not None else None
         self.dp = dev_plan(plan)
+
+
+# another consumer grid than the built-in one: a launch per group, a signalling GEMM
+PER_GROUP = {"consumer_blocks": 255}
+FORMS = pytest.mark.parametrize("opts", [None, PER_GROUP], ids=["default", "per_group"])
 
 
 def run(w, plan, d: Dev, *, overlap=True, opts=None):
@@ -91,7 +100,7 @@ def check(w, inp, plan, o, sample_rows=None, opts=None):
         rows = np.sort(np.random.default_rng(w.seed + 1000).choice(w.M, sample_rows, replace=False))
         ref = oracle.encode(oracle.gemm_exact(inp.A, inp.W, w.dtype, rows=rows), w.dtype)
         assert_close_bits(C_plain.reshape(w.M, w.N)[rows], ref, w.dtype, "GEMM (sampled rows)")
-    Cr, dst, out, counters, status = run(w, plan, d, overlap=True)
+    Cr, dst, out, counters, status = run(w, plan, d, overlap=True, opts=opts)
     assert status == 0
     # a plan of one group runs serialized and leaves the counters alone
     np.testing.assert_array_equal(counters, np.array(o.targets) if plan.P > 1 else np.zeros(plan.P, np.int64))
@@ -107,7 +116,7 @@ def check(w, inp, plan, o, sample_rows=None, opts=None):
     else:
         np.testing.assert_array_equal(out.reshape(w.M, w.N), x)
     # the same work serialized on one stream gives the same bits
-    Cr2, dst2, out2, counters2, status2 = run(w, plan, d, overlap=False)
+    Cr2, dst2, out2, counters2, status2 = run(w, plan, d, overlap=False, opts=opts)
     assert status2 == 0
     np.testing.assert_array_equal(Cr2, Cr)
     np.testing.assert_array_equal(dst2, dst)
@@ -125,8 +134,9 @@ SMALL = {
 }
 
 
+@FORMS
 @pytest.mark.parametrize("name", list(SMALL))
-def test_small_workloads(name):
+def test_small_workloads(name, opts):
     w = workloads.WORKLOADS[name]
     cus, sizes = 256, None
     if SMALL[name] is not None:
@@ -135,7 +145,7 @@ def test_small_workloads(name):
     say(f"[pipeline small] {w.name} cus={cus} sizes={sizes}")
     inp = workloads.make_inputs(w)
     plan, o = plan_for(w, inp, num_cus=cus, sizes=list(sizes) if sizes else None)
-    C_plain, out = check(w, inp, plan, o)
+    C_plain, out = check(w, inp, plan, o, opts=opts)
     # end to end against the oracle's own chain from the exact GEMM
     C_ref = oracle.gemm_ref(inp.A, inp.W, w.dtype)
     _, dst_ref, out_ref = oracle.run_path(o, C_ref, inp.peer if w.pattern != "subtoken" else None,
@@ -200,8 +210,9 @@ def random_cases(n, seed=2504):
     return out
 
 
+@FORMS
 @pytest.mark.parametrize("case", range(40))
-def test_random_paths(case):
+def test_random_paths(case, opts):
     # the whole path on seeded random small shapes: every check of
     # test_small_workloads' first part (GEMM against the exact product,
     # reorder, consumer and post-reorder against the oracle, serialized run
@@ -211,7 +222,7 @@ def test_random_paths(case):
         f"{w.pattern}/{w.num_dest} bias={w.bias} rms={w.rmsnorm} gamma={w.gamma} cus={cus} {unit} {sizes}")
     inp = workloads.make_inputs(w)
     plan, o = plan_for(w, inp, num_cus=cus, sizes=sizes, unit=unit)
-    check(w, inp, plan, o)
+    check(w, inp, plan, o, opts=opts)
 
 
 def dispatch_cases(n, seed=2505):
@@ -239,20 +250,22 @@ def dispatch_cases(n, seed=2505):
     return out
 
 
+@FORMS
 @pytest.mark.parametrize("case", range(24))
-def test_dispatch_orders(case):
+def test_dispatch_orders(case, opts):
     # the whole path (checks of test_random_paths) with the grouped and XCD
     # dispatch orders at random band heights and chiplet counts: the GEMM
     # computes the tile of each position itself, and must still run every
-    # tile exactly once (a tile missed leaves NaNs, a group short of its
-    # target leaves the consumer waiting) whatever the position classes
+    # tile exactly once (a tile missed leaves NaNs and, with a launch per
+    # group, a group short of its target leaves the consumer waiting) whatever
+    # the position classes
     w, cus, sizes, group_m, num_xcds = dispatch_cases(24)[case]
     say(f"[pipeline dispatch] {w.name} {w.M}x{w.N}x{w.K} {w.dtype} tile {w.tile_m}x{w.tile_n} {w.order} "
         f"group_m={group_m} num_xcds={num_xcds} {w.pattern}/{w.num_dest} bias={w.bias} cus={cus} {sizes}")
     inp = workloads.make_inputs(w)
     plan, o = plan_for(w, inp, num_cus=cus, sizes=sizes, unit="waves", group_m=group_m, num_xcds=num_xcds)
     np.testing.assert_array_equal(plan.order, np.array(o.order))
-    check(w, inp, plan, o)
+    check(w, inp, plan, o, opts=opts)
 
 
 FULL = {
@@ -334,8 +347,9 @@ def test_consumer_grid(grid, name):
         fo.set_consumer_grid(*old)
 
 
+@FORMS
 @pytest.mark.parametrize("name", ["rs_8192x8192x3584", "a2a_4096x7168x2048"])
-def test_plan_from_cache_runs_the_path(name):
+def test_plan_from_cache_runs_the_path(name, opts):
     # a size seen only at run time takes the partition cached for its nearest
     # neighbour (Section 4.2); the plan built from it runs the whole path
     M, N, K, cus, _ = SMALL[name]
@@ -359,7 +373,7 @@ def test_plan_from_cache_runs_the_path(name):
     assert tuple(plan.sizes) == sizes
     o = oracle.make_plan(w.M, w.N, w.tile_m, w.tile_n, num_cus=cus, order=w.order, pattern=w.pattern,
                          num_dest=nd, sigma=inp.sigma, bucket=inp.bucket, sizes=sizes, unit="waves")
-    check(w, inp, plan, o)
+    check(w, inp, plan, o, opts=opts)
 
 
 @pytest.mark.parametrize("limit", [8, 1])

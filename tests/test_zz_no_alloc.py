@@ -18,7 +18,7 @@ CASES = [("rs_8192x8192x3584", (1024, 1280, 512, 8, (2, 1))),
          ("rs_8192x8192x3584", (1024, 1280, 512, 8, (2, 1)))]
 
 
-def _run(w, inp, plan, dp, d, noalloc, s1, s2):
+def _run(w, inp, plan, dp, d, noalloc, s1, s2, opts):
     torch = torch_mod()
     n = w.M * w.N
     C, dst, out = empty16(n, w.dtype), empty16(plan.dest_elems, w.dtype), empty16(n, w.dtype)
@@ -26,16 +26,19 @@ def _run(w, inp, plan, dp, d, noalloc, s1, s2):
     torch.cuda.synchronize()
     if noalloc:
         fo.run_overlapped_noalloc(plan, dp, d["A"], d["W"], C, d["peer"], dst, out, d["bias"], d["gamma"], w.eps,
-                                  w.rmsnorm, status_word=status, gemm_stream=s1, comm_stream=s2)
+                                  w.rmsnorm, status_word=status, gemm_stream=s1, comm_stream=s2, opts=opts)
     else:
         counters = zeros_u32(plan.num_counters)
         fo.run_overlapped(plan, dp, d["A"], d["W"], C, d["peer"], dst, out, d["bias"], d["gamma"], w.eps,
-                          w.rmsnorm, counters, status, s1, s2)
+                          w.rmsnorm, counters, status, s1, s2, opts=opts)
     torch.cuda.synchronize()
     return from_dev(C)[:n], from_dev(dst)[:plan.dest_elems], from_dev(out)[:n], int(status.cpu()[0])
 
 
-def test_noalloc_matches_the_allocating_entry_point():
+# (short runs consume their groups together; another consumer grid than the
+# built-in one keeps a launch per group, which the GEMM signals in the static array)
+@pytest.mark.parametrize("opts", [None, {"consumer_blocks": 255}], ids=["default", "per_group"])
+def test_noalloc_matches_the_allocating_entry_point(opts):
     torch = torch_mod()
     assert torch.cuda.is_available(), "no GPU visible"
     fo.lib()
@@ -51,8 +54,8 @@ def test_noalloc_matches_the_allocating_entry_point():
              "peer": to_dev(inp.peer) if w.pattern != "subtoken" else None,
              "bias": to_dev(inp.bias) if inp.bias is not None else None,
              "gamma": to_dev(inp.gamma) if inp.gamma is not None else None}
-        ref = _run(w, inp, plan, dp, d, False, s1, s2)
-        got = _run(w, inp, plan, dp, d, True, s1, s2)
+        ref = _run(w, inp, plan, dp, d, False, s1, s2, opts)
+        got = _run(w, inp, plan, dp, d, True, s1, s2, opts)
         assert ref[3] == 0 and got[3] == 0, f"call {k}: status {ref[3]} / {got[3]}"
         for what, a, b in zip(("C'", "dst", "out"), got[:3], ref[:3]):
             np.testing.assert_array_equal(a, b, err_msg=f"call {k}: {what}")
