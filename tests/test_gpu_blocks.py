@@ -127,3 +127,76 @@ def test_bands_taller_than_the_output(tile, grid, order):
                     plain[oracle.reorder_index(o)] = got
                     assert_close_bits(plain, oracle.gemm_ref(A, W, "bf16").reshape(-1), "bf16", "GEMM")
                 np.testing.assert_array_equal(got, plain[oracle.reorder_index(o)], err_msg=f"{group_m} {xcds} {cus}")
+
+
+# tile rows and columns, compute units, reserved ones, order, band height, chiplets: 128x128 blocks (100 of them, and
+# grids that reach past the output) over few workgroups, and 64x64 blocks (tiles in (W, 2 W]) that the reserved units
+# keep from running in pairs
+ROUNDS = [(20, 20, 5, 0, "xcd", 4, 8), (19, 21, 12, 0, "grouped", 3, 1), (19, 21, 7, 0, "xcd", 5, 3),
+          (6, 9, 33, 3, "xcd", 4, 8), (7, 7, 27, 2, "grouped", 2, 1)]
+
+
+@pytest.mark.parametrize("rows,cols,cus,reserved,order,band,xcds", ROUNDS)
+@pytest.mark.parametrize("K", [64, 128, 192, 320])
+def test_signalled_blocks_in_rounds(rows, cols, cus, reserved, order, band, xcds, K):
+    # more blocks than workgroups: positions drawn from the position words, a
+    # block's counts sent during the next one's first steps (or, when the loop is
+    # shorter than the ring, ahead of it), the next block's loads ahead of the
+    # stores. Every producer mode, launches in a row that clear the group
+    # counters only, and runs with live consumers on a NaN-filled buffer: a count
+    # that is sent before its tile is stored lets one read the NaNs in C.
+    torch = torch_mod()
+    M, N, dtype = 64 * rows, 64 * cols, "fp16"
+    tiles, W = rows * cols, cus - reserved
+    blocks = (rows + 1) // 2 * ((cols + 1) // 2) if tiles > 2 * W else tiles
+    assert blocks > (2 * W if not reserved else W), "one block per workgroup"
+    say(f"[signalled blocks] {M}x{N}x{K} W={W} {order} {band} {xcds}")
+    rng = np.random.default_rng(K + tiles)
+    A = workloads.to_bits(rng.uniform(-1, 1, (M, K)), dtype)
+    Wt = workloads.to_bits(rng.uniform(-1, 1, (N, K)) / np.sqrt(K), dtype)
+    dA, dW = to_dev(A), to_dev(Wt)
+    peer = workloads.uniform_bits(M * N, 7, dtype)
+    dP = to_dev(peer)
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    plain_plan = fo.plan_groups(M, N, K, dtype=dtype, tile_m=64, tile_n=64, pattern="rowmajor", sizes=[-(-tiles // 256)])
+    C = empty16(M * N, dtype)
+    fo.gemm_signal_reorder(plain_plan, None, dA, dW, C, None)
+    torch.cuda.synchronize()
+    plain = from_dev(C)[:M * N]
+    assert_close_bits(plain, oracle.gemm_ref(A, Wt, dtype).reshape(-1), dtype, "GEMM")
+    T = -(-tiles // W)
+    sizes = [1, T - 1] if T < 3 else [1, T // 2, T - 1 - T // 2]
+    for pattern, nd in [("tile", 0), ("subtile", 4), ("subtoken", 3)]:
+        kw = dict(num_cus=cus, reserved_cus=reserved, order=order, group_m=band, num_xcds=xcds, pattern=pattern,
+                  num_dest=nd, sizes=sizes)
+        sigma = rng.permutation(nd) if pattern == "subtile" else None
+        bucket = rng.integers(0, nd, M) if pattern == "subtoken" else None
+        plan = fo.plan_groups(M, N, K, dtype=dtype, tile_m=64, tile_n=64, dest_perm=sigma, row_bucket=bucket, **kw)
+        o = oracle.make_plan(M, N, 64, 64, sigma=sigma, bucket=bucket, unit="waves", **kw)
+        assert plan.P > 1
+        dp, want = dev_plan(plan), plain[oracle.reorder_index(o)]
+        sums = oracle.apply_consumer(o, want, peer if pattern != "subtoken" else None, dtype)
+        for mode in (0, 1, 2):
+            ctr = zeros_u32(plan.num_counters)
+            for launch in range(3):
+                what = f"{pattern} mode {mode} launch {launch}"
+                C = empty16(M * N, dtype)
+                ctr[:plan.P].zero_()
+                torch.cuda.synchronize()
+                fo.gemm_signal_reorder(plan, dp, dA, dW, C, ctr, opts={"sync_producer": mode})
+                torch.cuda.synchronize()
+                np.testing.assert_array_equal(from_dev(C)[:M * N], want, err_msg=what)
+                c = ctr.cpu().numpy()
+                np.testing.assert_array_equal(c[:plan.P], np.array(o.targets), err_msg=what)
+                np.testing.assert_array_equal(c[plan.P:plan.P + fo.DISPENSER_WORDS], 0, err_msg=what)
+            C, dst, out, status = empty16(M * N, dtype), empty16(M * N, dtype), empty16(M * N, dtype), zeros_u32(1)
+            torch.cuda.synchronize()
+            fo.run_overlapped(plan, dp, dA, dW, C, dP if pattern != "subtoken" else None, dst, out, counters=ctr,
+                              status_word=status, gemm_stream=s1, comm_stream=s2,
+                              opts={"sync_producer": mode, "sync_consumer": mode, "consumer_blocks": 255})
+            torch.cuda.synchronize()
+            what = f"{pattern} mode {mode} with consumers"
+            assert int(status.cpu()[0]) == 0, what
+            np.testing.assert_array_equal(from_dev(C)[:M * N], want, err_msg=what)
+            np.testing.assert_array_equal(from_dev(dst)[:M * N], sums, err_msg=what)
+            np.testing.assert_array_equal(from_dev(out)[:M * N], sums[oracle.post_index(o)], err_msg=what)

@@ -318,7 +318,9 @@ def test_tile_trace():
 
 @pytest.mark.parametrize("order,tile,shape,cus", [("xcd", (256, 256), (1024, 1280, 512), 8),
                                                   ("xcd", (256, 128), (1024, 1024, 256), 8),
-                                                  ("rowmajor", (64, 64), (256, 256, 128), 4)])
+                                                  ("rowmajor", (64, 64), (256, 256, 128), 4),
+                                                  ("rowmajor", (64, 64), (1216, 1344, 128), 6),
+                                                  ("xcd", (64, 64), (1216, 1344, 320), 6)])
 def test_back_to_back_launches_need_no_dispenser_reset(order, tile, shape, cus):
     # launches on one counters array whose position words are never cleared
     # in between (only the group counters are): each launch must leave them
