@@ -4,15 +4,15 @@ Short runs consume all groups together when the options leave the consumer
 launches alone, so these small runs would not reach the per-group launches and
 their final launch's count. With another consumer grid as the process default
 they do. All tests run on one pair of streams that are on different hardware
-queues (kernels of streams that share a queue run one after another, and a held
-stream then holds the other one too).
+queues.
 """
 import itertools
 
 import pytest
 
 import paper_2504_19519_amd as fo
-from gpu_util import torch_mod
+import test_gpu_handoff
+from gpu_util import streams_apart, torch_mod
 from test_gpu_handoff import (gpu, test_a_held_stream_is_waited_for,  # noqa: F401
                               test_a_timed_out_run_does_not_count_for_the_next, test_back_to_back_runs_share_buffers,
                               test_stale_counter_words_do_not_reach_a_run, test_timed_out_handoffs_raise_the_status_bit,
@@ -21,31 +21,28 @@ from test_gpu_handoff import (gpu, test_a_held_stream_is_waited_for,  # noqa: F4
 pytestmark = pytest.mark.gpu
 
 
-def _apart(torch, a, b):
-    """Whether b runs while a is held, and a while b is."""
-    for held, free in ((a, b), (b, a)):
-        torch.cuda.synchronize()
-        eh, ef = torch.cuda.Event(), torch.cuda.Event()
-        with torch.cuda.stream(held):
-            torch.cuda._sleep(20_000_000)
-        eh.record(held)
-        ef.record(free)
-        ef.synchronize()
-        if eh.query():
-            return False
-    torch.cuda.synchronize()
-    return True
+class _With:
+    """An object with some of its attributes replaced."""
+
+    def __init__(self, base, **attributes):
+        self.__dict__.update(attributes, _base=base)
+
+    def __getattr__(self, name):
+        return getattr(self._base, name)
 
 
-@pytest.fixture(scope="module", autouse=True)
-def a_launch_per_group(gpu):  # noqa: F811
-    torch = torch_mod()
-    streams = [torch.cuda.Stream() for _ in range(6)]
-    pair = next(p for p in itertools.combinations(streams, 2) if _apart(torch, *p))
-    old, Stream = fo.get_consumer_grid(), torch.cuda.Stream
+@pytest.fixture(scope="module")
+def pair(gpu):  # noqa: F811
+    return streams_apart()
+
+
+@pytest.fixture(autouse=True)
+def a_launch_per_group(pair, monkeypatch):
+    # (the tests' own module sees a torch whose new streams are the pair's)
+    torch, turn = torch_mod(), itertools.cycle(pair)
+    view = _With(torch, cuda=_With(torch.cuda, Stream=lambda: next(turn)))
+    monkeypatch.setattr(test_gpu_handoff, "torch_mod", lambda: view)
+    old = fo.get_consumer_grid()
     fo.set_consumer_grid(255, 64)
-    turn = itertools.cycle(pair)
-    torch.cuda.Stream = lambda **kw: Stream(**kw) if kw else next(turn)
     yield
-    torch.cuda.Stream = Stream
     fo.set_consumer_grid(*old)
