@@ -17,7 +17,7 @@
 // Measured against one 64x64 form for all (four waves of 32x32, three stages,
 // one workgroup per compute unit, bf16): 768x3840x4160 51.9 -> 29.0 us (473 ->
 // 846 TFLOP/s), signalled 1216x2880x1984 47.6 -> 22.6 us, 64x4096x3584 17.0 ->
-// 9.8 us. What bounds it now: in the 128x128 form the LDS (32 KB in, 64 KB read
+// 9.8 us (in a run of 14.9 us; 13.3 without the loop, see Mode). What bounds it now: in the 128x128 form the LDS (32 KB in, 64 KB read
 // per 512 cycles of MFMA) and the ~5 us of a launch's prologue and epilogue; in
 // the small blocks the latency of a step's barrier and fragment reads.
 //
@@ -83,8 +83,19 @@ __device__ __forceinline__ int32_t table_at(const int32_t* t, int64_t i) {
     return ((const __attribute__((address_space(4))) int32_t*)(uintptr_t)t)[i];
 }
 
-template <int DT, int TM, int TN, int BM, int BN, int ST, int KS>
+// What a launch may do: anything; no counters and no trace; and a block per
+// workgroup besides. The loop over blocks with all that it may do has some 75
+// scalars that are formed, and spilled, between a launch's start and its first MFMA,
+// which short launches wait for (fp16 us, kAny -> kOne: 64x64, 256 tiles, K 64 5.06
+// -> 3.44, K 1024 7.15 -> 5.54, K 4096 16.5 -> 14.6; 64x32, 128 tiles, K 64 4.80 ->
+// 3.37, K 1024 6.47 -> 5.02; 32x32, 64 tiles, K 64 4.56 -> 3.07, K 3584 9.4 -> 7.9;
+// kAny -> kPlain: 64x64, 320 tiles on 240 workgroups, K 512 8.5 -> 7.2). The
+// 128x128 form has one body for all: its launches are longer.
+enum Mode { kAny, kPlain, kOne };
+
+template <int DT, int TM, int TN, int BM, int BN, int ST, int KS, Mode MODE>
 __device__ __forceinline__ void block_body(const GemmArgs& a) {
+    constexpr bool ONE = MODE == kOne;
     constexpr int kWaves = 4;                          // 2 x 2
     constexpr int WTM = BM / 2, WTN = BN / 2;          // a wave's part of the block
     constexpr int MI = WTM / 16, NJ = WTN / 16;
@@ -126,10 +137,12 @@ __device__ __forceinline__ void block_body(const GemmArgs& a) {
     // Block positions are handed out as in the other GEMM kernels (gemm.hip):
     // from the class's atomic counter, the workgroup that draws a class's last
     // value leaves the word zero; without a dispenser, a fixed stride.
+    const bool signals = MODE == kAny && a.counters, traced = MODE == kAny && a.trace;
+    const bool dispenser = MODE == kAny && a.dispenser;
     const int DC = a.num_dispensers;
-    const int cls = a.dispenser ? (int)(blockIdx.x % (unsigned)DC) : 0;
-    const uint32_t n_cls = a.dispenser ? (uint32_t)((blocks - cls + DC - 1) / DC) : 0u;
-    const uint32_t w_cls = a.dispenser ? (uint32_t)(((int)gridDim.x - cls + DC - 1) / DC) : 0u;
+    const int cls = dispenser ? (int)(blockIdx.x % (unsigned)DC) : 0;
+    const uint32_t n_cls = dispenser ? (uint32_t)((blocks - cls + DC - 1) / DC) : 0u;
+    const uint32_t w_cls = dispenser ? (uint32_t)(((int)gridDim.x - cls + DC - 1) / DC) : 0u;
     // (per-lane address: at a uniform one the compiler broadcasts the result
     // across the wave, waiting for it and for every load in flight at once)
     auto draw = [&]() -> uint32_t {
@@ -142,7 +155,7 @@ __device__ __forceinline__ void block_body(const GemmArgs& a) {
             __hip_atomic_store(a.dispenser + cls, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return v < n_cls ? cls + DC * (int)v : blocks;
     };
-    const bool coherent = a.counters && a.sync == FO_SYNC_COHERENT;
+    const bool coherent = signals && a.sync == FO_SYNC_COHERENT;
 
     // A load instruction fills 1 KB: 8 operand rows of 128 bytes, chunk c of
     // row r at slot c ^ ((r / 2) % 8).
@@ -253,12 +266,12 @@ __device__ __forceinline__ void block_body(const GemmArgs& a) {
     };
 
     int p = (int)blockIdx.x;
-    if (tid < 2) s_arrived[tid] = 0;
+    if (!ONE && tid < 2) s_arrived[tid] = 0;
     // One block per workgroup (the hardware starts workgroups in order): no
     // positions to hand out, and the words stay zero.
-    const bool dispense = a.dispenser && (int)gridDim.x < blocks;
+    const bool dispense = dispenser && (int)gridDim.x < blocks;
     if (dispense && tid == 0) s_pos[1] = position(draw());
-    wait_and_barrier<63>();
+    if constexpr (!ONE) wait_and_barrier<63>();
     if (dispense) p = __builtin_amdgcn_readfirstlane(s_pos[1]);
 
     // The wave's part of the current block: its first row and column, its plan
@@ -284,7 +297,7 @@ __device__ __forceinline__ void block_body(const GemmArgs& a) {
         if (inside) {
             const int tile = row0 / TM * a.tiles_n + col0 / TN;
             slot = a.tile_to_slot ? table_at(a.tile_to_slot, tile) : 0;
-            group = a.slot_group ? table_at(a.slot_group, slot) : 0;
+            if ((signals || a.pattern == FO_PATTERN_SUBTILE) && a.slot_group) group = table_at(a.slot_group, slot);
             if (a.pattern == FO_PATTERN_SUBTOKEN && lane < WTM) {
                 bucket = a.row_bucket[row0 + lane];
                 rank = a.row_rank[row0 + lane];
@@ -343,9 +356,9 @@ __device__ __forceinline__ void block_body(const GemmArgs& a) {
 
     int parity = 0;
     bool pend = false;              // the previous block's counts are still to be sent
-    if (p < blocks) start();
-    while (p < blocks) {
-        const uint64_t t_start = a.trace ? wall_clock64() : 0;
+    if (ONE || p < blocks) start();
+    while (ONE || p < blocks) {
+        const uint64_t t_start = traced ? wall_clock64() : 0;
         uint32_t ticket = 0;
         if (dispense && tid == 0) ticket = draw();   // used after the main loop
 #pragma unroll
@@ -385,7 +398,7 @@ __device__ __forceinline__ void block_body(const GemmArgs& a) {
         const bool inside_now = inside;
         p = __builtin_amdgcn_readfirstlane(next);
         // the next block's first loads go out ahead of this block's stores
-        if (p < blocks) start();
+        if (!ONE && p < blocks) start();
 
         if (inside_now) {
             if constexpr (WTN == 16) {
@@ -440,10 +453,11 @@ __device__ __forceinline__ void block_body(const GemmArgs& a) {
                 }
             }
         }
-        if (a.counters) {
+        if constexpr (ONE) return;
+        if (signals) {
             // (waves of a 64x64 block: one tile, counted once)
             if (lane == 0) s_group[parity][wave] = inside_now && (kOwnTile || wave == 0) ? group_now : -1;
-            if (coherent && !a.trace && p < blocks) {
+            if (coherent && !traced && p < blocks) {
                 pend = true;               // sent after the next block's first steps
             } else {
                 if (a.sync == FO_SYNC_FENCE_ALL) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
@@ -453,7 +467,7 @@ __device__ __forceinline__ void block_body(const GemmArgs& a) {
                 arrive(parity);
             }
         }
-        if (!kOwnTile && a.trace && p_now < a.trace_cap) {   // (blocks in plan order: p is the dispatch position)
+        if (!kOwnTile && traced && p_now < a.trace_cap) {   // (blocks in plan order: p is the dispatch position)
             __builtin_amdgcn_s_waitcnt(wait_imm(0, 0));
             __syncthreads();
             if (tid == 0) {
@@ -470,11 +484,11 @@ __device__ __forceinline__ void block_body(const GemmArgs& a) {
 }
 
 // Template arguments: dtype, block rows and columns, waves, stages, k values
-// per step, plan tile.
-template <int DT, int BM, int BN, int WM, int WN, int ST, int BK, int TM, int TN>
+// per step, plan tile, what the launch may do.
+template <int DT, int BM, int BN, int WM, int WN, int ST, int BK, int TM, int TN, Mode MODE = kAny>
 __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_signal_kernel(const GemmArgs a) {
     static_assert(WM == 2 && WN == 2 && BK % 64 == 0, "2 x 2 waves");
-    block_body<DT, TM, TN, BM, BN, ST, BK / 64>(a);
+    block_body<DT, TM, TN, BM, BN, ST, BK / 64, MODE>(a);
 }
 
 // 128x128 blocks of plan tiles TM x TN, one or two on a compute unit.
@@ -494,13 +508,18 @@ void launch_128(const GemmArgs& a, int grid, bool pair, hipStream_t s) {
 // steps of 128, since their MFMAs are too few to cover a barrier per 64 (64x32
 // 128x4096x3584 12.6, in steps of 64 15.7; 32x32 64x4096x3584 9.8, 11.2).
 template <int DT>
-void launch_64(const GemmArgs& a, int bm, int bn, int grid, bool pair, hipStream_t s) {
+void launch_64(const GemmArgs& a, int bm, int bn, int grid, bool pair, bool one, hipStream_t s) {
     const dim3 g(grid), b(256);
     if (bm == 128) launch_128<DT, 64, 64>(a, grid, pair, s);
+    else if (bm == 64 && bn == 64 && one)
+        hipLaunchKernelGGL((gemm_signal_kernel<DT, 64, 64, 2, 2, 4, 64, 64, 64, kOne>), g, b, 0, s, a);
+    else if (bm == 64 && bn == 64 && !a.counters && !a.trace)
+        hipLaunchKernelGGL((gemm_signal_kernel<DT, 64, 64, 2, 2, 4, 64, 64, 64, kPlain>), g, b, 0, s, a);
     else if (bm == 64 && bn == 64)
         hipLaunchKernelGGL((gemm_signal_kernel<DT, 64, 64, 2, 2, 4, 64, 64, 64>), g, b, 0, s, a);
-    else if (bm == 64) hipLaunchKernelGGL((gemm_signal_kernel<DT, 64, 32, 2, 2, 3, 128, 64, 64>), g, b, 0, s, a);
-    else hipLaunchKernelGGL((gemm_signal_kernel<DT, 32, 32, 2, 2, 4, 128, 64, 64>), g, b, 0, s, a);
+    else if (bm == 64)
+        hipLaunchKernelGGL((gemm_signal_kernel<DT, 64, 32, 2, 2, 3, 128, 64, 64, kOne>), g, b, 0, s, a);
+    else hipLaunchKernelGGL((gemm_signal_kernel<DT, 32, 32, 2, 2, 4, 128, 64, 64, kOne>), g, b, 0, s, a);
 }
 
 // Whether 128x128 blocks run in pairs on a compute unit. A pair takes about 1.7
@@ -526,6 +545,7 @@ bool in_pairs(const GemmArgs& a, int64_t blocks, int64_t W, bool share_cus) {
 //   tiles <= 2 W   64x64   256 tiles, K 1024: 7.7 (64x32 8.9, 128x128 11.5);
 //                          336 tiles, K 2048: 14.9 (16.4 in 128x128, 18.1 one
 //                          block per compute unit); 512 tiles: 26.2 (26.9)
+//                          (these three 1.5 less since in the kOne form)
 //   above          128x128 720 tiles, K 4160: 29.0 (64x64 38.5);
 //                          2272 tiles, K 1920: 48.7 (57.2)
 // Parts of a tile have no count of their own: a signalled launch takes whole
@@ -549,8 +569,9 @@ hipError_t launch_gemm64(int dtype, GemmArgs a, int wave_width, bool share_cus, 
     const bool pair = bm == 128 ? in_pairs(a, blocks, W, share_cus) : bn == 64 && share_cus && !a.trace;
     const int grid = (int)std::min<int64_t>(blocks, pair ? 2 * W : W);
     a.num_dispensers = std::max(1, std::min(a.num_dispensers, grid));
-    if (dtype == FO_FP16) launch_64<FO_FP16>(a, bm, bn, grid, pair, s);
-    else launch_64<FO_BF16>(a, bm, bn, grid, pair, s);
+    const bool one = !a.counters && !a.trace && grid == blocks;
+    if (dtype == FO_FP16) launch_64<FO_FP16>(a, bm, bn, grid, pair, one, s);
+    else launch_64<FO_BF16>(a, bm, bn, grid, pair, one, s);
     return hipGetLastError();
 }
 

@@ -176,6 +176,11 @@ def test_signalled_blocks_in_rounds(rows, cols, cus, reserved, order, band, xcds
         assert plan.P > 1
         dp, want = dev_plan(plan), plain[oracle.reorder_index(o)]
         sums = oracle.apply_consumer(o, want, peer if pattern != "subtoken" else None, dtype)
+        C = empty16(M * N, dtype)                 # the unsignalled kernel's loop over blocks
+        torch.cuda.synchronize()
+        fo.gemm_signal_reorder(plan, dp, dA, dW, C, None)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(from_dev(C)[:M * N], want, err_msg=f"{pattern} unsignalled")
         for mode in (0, 1, 2):
             ctr = zeros_u32(plan.num_counters)
             for launch in range(3):
