@@ -131,4 +131,35 @@ inline bool consumed_together(const fo_plan& p, bool sum, int64_t limit_us) {
     return (gemm_us < 300.0 || gemm_us < 3.0 * consume_us) && (double)limit_us >= 100.0 * gemm_us && limit_us >= 10000;
 }
 
+// Whether an unsignalled GEMM of plans with 256 x tile_n tiles computes 128x128
+// blocks instead of whole tiles: where the tiles' last wave is emptier than the
+// blocks' or one tile per compute unit covers its barriers less than a pair of
+// blocks (bf16, us per launch, K 4096 / 1024, tiles -> blocks):
+//   256x128  0.5 W  52 -> 32 / 18 -> 12    0.75 W  55 -> 48 / 19 -> 17
+//            W      60 -> 57 / 20 -> 18    1.25 W 107 -> 85 / 34 -> 28
+//            2 W   121 -> 119 / 37 -> 34   (8 W, K 3584: 430 us in tiles, 480 by
+//            the rate of 4 W in blocks: the clock is power-limited there and the
+//            larger tile reads less per flop)
+//   256x256  0.25 W 72 -> 33 / 25 -> 13    0.5 W   74 -> 57 / 26 -> 19
+//            0.75 W 82 -> 90 / 28 -> 29    W      101 -> 119 / 32 -> 34
+//            1.25 W 168 -> 158 / 52 -> 45  1.5 W  178 -> 182 / 55 -> 51
+//            1.75 W 190 -> 214 / 57 -> 59
+// Where blocks may not run in pairs (compute units reserved), they take a round of
+// single blocks for W of them, 0.6 of a round of 256x128 tiles and 0.4 of one of
+// 256x256 (W = 240, fp16, K 4096 / 1024, tiles -> blocks):
+//   256x128  0.5 W   53 -> 34 / 18.0 -> 12.8  0.53 W 51.9 -> 52.8 / K 256 9.5 -> 11.7
+//            W       62 -> 65 / 20.4 -> 22.2  1.25 W 106 -> 89 / 33.8 -> 29.6
+//            1.5 W  109 -> 96 / 34.5 -> 31.9  2 W      - / 38.3 -> 41.0
+//   256x256  0.25 W  72 -> 34 / 24.9 -> 12.6  0.5 W   75 -> 65 / 25.9 -> 22.6
+//            1.04 W 161 -> 145 / -            1.25 W 163 -> 156 / -
+//            1.33 W   - / 51.2 -> 54.2
+inline bool takes_parts(int tile_n, int64_t tiles, int64_t W, int64_t K, bool share_cus) {
+    if (!share_cus) {
+        const int64_t rounds = (tiles + W - 1) / W, block_rounds = (tiles * (tile_n / 64) + W - 1) / W;
+        return tile_n == 128 ? tiles <= 2 * W && 4 * block_rounds < 7 * rounds : block_rounds < 3 * rounds;
+    }
+    if (tile_n == 128) return tiles <= 2 * W;
+    return 2 * tiles <= W || (tiles > W && (4 * tiles <= 5 * W || (K <= 1024 && 2 * tiles <= 3 * W)));
+}
+
 }  // namespace fo

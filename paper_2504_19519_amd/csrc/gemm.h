@@ -13,8 +13,8 @@ struct GemmArgs {
     int64_t M, N, K;
     int32_t tiles_m, tiles_n;
     int32_t order, group_m, num_xcds;
-    int32_t blocks_m, blocks_n;    // block grid and band height of the 64x64 plans' kernels (gemm_block.hip)
-    int32_t block_band;
+    int32_t blocks_m, blocks_n;    // block grid and band height of the kernels in gemm_block.hip (64x64 plans,
+    int32_t block_band;            // and parts of larger tiles)
     int32_t pattern, num_dest;
     const int32_t* tile_to_slot;   // device plan tables (may be null for ROWMAJOR)
     const int32_t* slot_group;
@@ -39,7 +39,7 @@ hipError_t launch_gemm(int dtype, int tile_m, int tile_n, const GemmArgs& a, int
 hipError_t launch_gemm64(int dtype, GemmArgs a, int wave_width, bool share_cus, hipStream_t s);
 // Plans with 256x128 and 256x256 tiles in 128x128 blocks (gemm_block.hip), and
 // whether a launch should take them.
-bool gemm_in_parts(int tile_n, const GemmArgs& a, int wave_width);
+bool gemm_in_parts(int tile_n, const GemmArgs& a, int wave_width, bool share_cus);
 hipError_t launch_gemm_parts(int dtype, int tile_n, GemmArgs a, int wave_width, bool share_cus, hipStream_t s);
 bool gemm_tile_supported(int tile_m, int tile_n);
 

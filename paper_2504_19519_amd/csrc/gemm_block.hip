@@ -575,24 +575,11 @@ hipError_t launch_gemm64(int dtype, GemmArgs a, int wave_width, bool share_cus, 
     return hipGetLastError();
 }
 
-// 128x128 blocks instead of whole larger tiles (unsignalled launches only: a
-// part has no count), where the tiles' last wave is emptier than the blocks' or
-// one tile per compute unit covers its barriers less than a pair of blocks
-// (bf16, us per launch, K 4096 / 1024, tiles -> blocks):
-//   256x128  0.5 W  52 -> 32 / 18 -> 12    0.75 W  55 -> 48 / 19 -> 17
-//            W      60 -> 57 / 20 -> 18    1.25 W 107 -> 85 / 34 -> 28
-//            2 W   121 -> 119 / 37 -> 34   (8 W, K 3584: 430 us in tiles, 480 by
-//            the rate of 4 W in blocks: the clock is power-limited there and the
-//            larger tile reads less per flop)
-//   256x256  0.25 W 72 -> 33 / 25 -> 13    0.5 W   74 -> 57 / 26 -> 19
-//            0.75 W 82 -> 90 / 28 -> 29    W      101 -> 119 / 32 -> 34
-//            1.25 W 168 -> 158 / 52 -> 45  1.5 W  178 -> 182 / 55 -> 51
-//            1.75 W 190 -> 214 / 57 -> 59
-bool gemm_in_parts(int tile_n, const GemmArgs& a, int wave_width) {
-    if (a.counters || a.trace) return false;
-    const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n, W = wave_width;
-    if (tile_n == 128) return tiles <= 2 * W;
-    return 2 * tiles <= W || (tiles > W && (4 * tiles <= 5 * W || (a.K <= 1024 && 2 * tiles <= 3 * W)));
+// By the rule of takes_parts; unsignalled, untraced launches only (a part has no
+// count and no position of its own).
+bool gemm_in_parts(int tile_n, const GemmArgs& a, int wave_width, bool share_cus) {
+    return !a.counters && !a.trace &&
+           takes_parts(tile_n, (int64_t)a.tiles_m * a.tiles_n, wave_width, a.K, share_cus);
 }
 
 hipError_t launch_gemm_parts(int dtype, int tile_n, GemmArgs a, int wave_width, bool share_cus, hipStream_t s) {

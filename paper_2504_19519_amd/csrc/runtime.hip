@@ -426,7 +426,7 @@ fo_status fo_gemm_signal_reorder(const fo_plan* plan, const void* dev_plan, cons
     const int width = std::max(plan->W, 1);
     hipError_t e = plan->tile_m == 64
                        ? fo::launch_gemm64(plan->dtype, a, width, plan->reserved_cus == 0, (hipStream_t)stream)
-                   : fo::gemm_in_parts(plan->tile_n, a, width)
+                   : fo::gemm_in_parts(plan->tile_n, a, width, plan->reserved_cus == 0)
                        ? fo::launch_gemm_parts(plan->dtype, plan->tile_n, a, width, plan->reserved_cus == 0,
                                                (hipStream_t)stream)
                        : fo::launch_gemm(plan->dtype, plan->tile_m, plan->tile_n, a, grid, (hipStream_t)stream);

@@ -58,9 +58,10 @@ def test_block_forms(dtype, K):
                     np.testing.assert_array_equal(c[plan.P:plan.P + fo.DISPENSER_WORDS], 0, err_msg=what)
 
 
+@pytest.mark.parametrize("reserved", [0, 3])        # (with reserved units, blocks run one to a unit)
 @pytest.mark.parametrize("tile_n,widths", [(128, [12, 11, 5, 4]), (256, [24, 12, 11, 5, 4])])
 @pytest.mark.parametrize("dtype,K", [("fp16", 64), ("bf16", 192), ("fp16", 448)])
-def test_parts_of_larger_tiles(tile_n, widths, dtype, K):
+def test_parts_of_larger_tiles(tile_n, widths, dtype, K, reserved):
     # 6 tiles of 256 x tile_n: unsignalled launches take 128x128 blocks where
     # the last wave is emptier in whole tiles (at most W / 2, and just past W),
     # signalled ones whole tiles; the bits are the same
@@ -77,9 +78,11 @@ def test_parts_of_larger_tiles(tile_n, widths, dtype, K):
             sigma = rng.permutation(nd) if pattern == "subtile" else None
             bucket = rng.integers(0, nd, M) if pattern == "subtoken" else None
             sizes = [1] * -(-6 // cus)
-            plan = fo.plan_groups(M, N, K, dtype=dtype, tile_m=256, tile_n=tile_n, num_cus=cus, pattern=pattern,
+            plan = fo.plan_groups(M, N, K, dtype=dtype, tile_m=256, tile_n=tile_n, num_cus=cus + reserved,
+                                  reserved_cus=reserved, pattern=pattern,
                                   num_dest=nd, dest_perm=sigma, row_bucket=bucket, sizes=sizes)
-            o = oracle.make_plan(M, N, 256, tile_n, num_cus=cus, order="xcd", group_m=4, num_xcds=8, pattern=pattern,
+            o = oracle.make_plan(M, N, 256, tile_n, num_cus=cus + reserved, reserved_cus=reserved, order="xcd",
+                                 group_m=4, num_xcds=8, pattern=pattern,
                                  num_dest=nd, sigma=sigma, bucket=bucket, sizes=sizes, unit="waves")
             dp = dev_plan(plan)
             for counters in (None, zeros_u32(plan.num_counters)):
