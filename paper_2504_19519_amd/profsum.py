@@ -28,7 +28,7 @@ import re
 import sys
 
 PKG = os.path.dirname(os.path.abspath(__file__))
-GEMM_SOURCES = ["csrc/gemm.hip", "csrc/gemm.h", "csrc/fo_device.h", "csrc/fo_internal.h"]
+GEMM_SOURCES = ["csrc/gemm.hip", "csrc/gemm_block.hip", "csrc/gemm.h", "csrc/fo_device.h", "csrc/fo_internal.h"]
 
 
 def gemm_sources_sha256() -> str:
