@@ -25,9 +25,10 @@
 //                       wider rows; which of bias, RMSNorm and gamma run is a
 //                       compile-time choice.
 // Each also in a fused form that is the consumer as well, for runs on one
-// stream: it reads the GEMM's output and the peer's partial and writes the
-// consumer's buffer and the output. Both are bound by memory: 8192x8192
-// restore 52 us and fused 89 us (5.2 and 6.0 TB/s; a large copy reaches 5.1).
+// stream and for overlapped runs whose groups are consumed together: it reads
+// the GEMM's output and the peer's partial and writes the consumer's buffer and
+// the output. Both are bound by memory: 8192x8192 restore 49 us and fused 89 us
+// (5.5 and 6.0 TB/s; a large copy reaches 5.1).
 // Sources are read through the caches (the consumer has just written them,
 // so part of them is still in the memory-side cache); the output is written
 // nontemporal.
