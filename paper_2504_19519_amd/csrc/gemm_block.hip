@@ -84,14 +84,18 @@ __device__ __forceinline__ int32_t table_at(const int32_t* t, int64_t i) {
 }
 
 // What a launch may do: anything; no counters and no trace; and a block per
-// workgroup besides. The loop over blocks with all that it may do has some 75
-// scalars that are formed, and spilled, between a launch's start and its first MFMA,
-// which short launches wait for (fp16 us, kAny -> kOne: 64x64, 256 tiles, K 64 5.06
-// -> 3.44, K 1024 7.15 -> 5.54, K 4096 16.5 -> 14.6; 64x32, 128 tiles, K 64 4.80 ->
-// 3.37, K 1024 6.47 -> 5.02; 32x32, 64 tiles, K 64 4.56 -> 3.07, K 3584 9.4 -> 7.9;
-// kAny -> kPlain: 64x64, 320 tiles on 240 workgroups, K 512 8.5 -> 7.2). The
-// 128x128 form has one body for all: its launches are longer.
-enum Mode { kAny, kPlain, kOne };
+// workgroup besides; counters in the default mode, an output in 31-bit range and no
+// trace. The loop over blocks with all that it may do has some 75 scalars that are
+// formed, and spilled, between a launch's start and its first MFMA, which short
+// launches wait for (64x64, 64x32 and 32x32 blocks, fp16, us):
+//   kAny -> kOne     64x64, 256 tiles, K 64 5.06 -> 3.44, K 1024 7.15 -> 5.54, K 4096
+//                    16.5 -> 14.6; 64x32, 128 tiles, K 64 4.80 -> 3.37, K 1024 6.47 ->
+//                    5.02; 32x32, 64 tiles, K 64 4.56 -> 3.07, K 3584 9.4 -> 7.9
+//   kAny -> kPlain   64x64, 320 tiles on 240 workgroups, K 512 8.5 -> 7.2
+//   kAny -> kSignal  64x64, 256 tiles, K 64 8.0 -> 7.2; on 240 workgroups, K 1024 12.5
+//                    -> 11.6; 512 tiles, K 4096 29.9 -> 29.2
+// The 128x128 form has one body for all: its launches are longer.
+enum Mode { kAny, kPlain, kOne, kSignal };
 
 template <int DT, int TM, int TN, int BM, int BN, int ST, int KS, Mode MODE>
 __device__ __forceinline__ void block_body(const GemmArgs& a) {
@@ -137,8 +141,8 @@ __device__ __forceinline__ void block_body(const GemmArgs& a) {
     // Block positions are handed out as in the other GEMM kernels (gemm.hip):
     // from the class's atomic counter, the workgroup that draws a class's last
     // value leaves the word zero; without a dispenser, a fixed stride.
-    const bool signals = MODE == kAny && a.counters, traced = MODE == kAny && a.trace;
-    const bool dispenser = MODE == kAny && a.dispenser;
+    const bool signals = MODE == kSignal || (MODE == kAny && a.counters), traced = MODE == kAny && a.trace;
+    const bool dispenser = MODE == kSignal || (MODE == kAny && a.dispenser);
     const int DC = a.num_dispensers;
     const int cls = dispenser ? (int)(blockIdx.x % (unsigned)DC) : 0;
     const uint32_t n_cls = dispenser ? (uint32_t)((blocks - cls + DC - 1) / DC) : 0u;
@@ -155,7 +159,7 @@ __device__ __forceinline__ void block_body(const GemmArgs& a) {
             __hip_atomic_store(a.dispenser + cls, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return v < n_cls ? cls + DC * (int)v : blocks;
     };
-    const bool coherent = signals && a.sync == FO_SYNC_COHERENT;
+    const bool coherent = MODE == kSignal || (signals && a.sync == FO_SYNC_COHERENT);
 
     // A load instruction fills 1 KB: 8 operand rows of 128 bytes, chunk c of
     // row r at slot c ^ ((r / 2) % 8).
@@ -336,7 +340,7 @@ __device__ __forceinline__ void block_body(const GemmArgs& a) {
             kWaves - 1)
             return;
         __hip_atomic_store(&s_arrived[parity], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (a.sync == FO_SYNC_FENCE_ONE) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        if (MODE == kAny && a.sync == FO_SYNC_FENCE_ONE) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         int g[kWaves];
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) g[w] = s_group[parity][w];
@@ -435,7 +439,7 @@ __device__ __forceinline__ void block_body(const GemmArgs& a) {
                         const u32x4_t v =
                             *reinterpret_cast<const u32x4_t*>(st + rr * WTN * 2 + ((c ^ (rr & (kCh - 1))) << 4));
                         const int64_t at = s_off[wave][16 * i + rr] + 8 * c;
-                        if (coherent && a.c_rsrc) {
+                        if (coherent && (MODE == kSignal || a.c_rsrc)) {
                             const __amdgpu_buffer_rsrc_t rC =
                                 __builtin_amdgcn_make_buffer_rsrc((void*)a.C, 0, 0x7FFFFFFF, kRsrcWord3);
                             __builtin_amdgcn_raw_buffer_store_b128(v, rC, (uint32_t)(at * 2), 0, kCachePolicySc1);
@@ -460,7 +464,7 @@ __device__ __forceinline__ void block_body(const GemmArgs& a) {
             if (coherent && !traced && p < blocks) {
                 pend = true;               // sent after the next block's first steps
             } else {
-                if (a.sync == FO_SYNC_FENCE_ALL) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                if (MODE == kAny && a.sync == FO_SYNC_FENCE_ALL) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
                 asm volatile("" ::: "memory");
                 __builtin_amdgcn_s_waitcnt(wait_imm(0, 0));
                 asm volatile("" ::: "memory");
@@ -515,6 +519,8 @@ void launch_64(const GemmArgs& a, int bm, int bn, int grid, bool pair, bool one,
         hipLaunchKernelGGL((gemm_signal_kernel<DT, 64, 64, 2, 2, 4, 64, 64, 64, kOne>), g, b, 0, s, a);
     else if (bm == 64 && bn == 64 && !a.counters && !a.trace)
         hipLaunchKernelGGL((gemm_signal_kernel<DT, 64, 64, 2, 2, 4, 64, 64, 64, kPlain>), g, b, 0, s, a);
+    else if (bm == 64 && bn == 64 && a.counters && !a.trace && a.sync == FO_SYNC_COHERENT && a.c_rsrc)
+        hipLaunchKernelGGL((gemm_signal_kernel<DT, 64, 64, 2, 2, 4, 64, 64, 64, kSignal>), g, b, 0, s, a);
     else if (bm == 64 && bn == 64)
         hipLaunchKernelGGL((gemm_signal_kernel<DT, 64, 64, 2, 2, 4, 64, 64, 64>), g, b, 0, s, a);
     else if (bm == 64)
