@@ -125,13 +125,19 @@ def test_reordered_output_is_permuted_plain_output(pattern, nd, dtype, sizes, ti
     np.testing.assert_array_equal(counters.cpu().numpy()[:plan.P], np.array(o.targets))
 
 
+# aligned default calls stream through the LDS ring; a cap of the whole grid takes
+# the kernels of an overlapped run's groups (16-byte, 8-byte and single accesses)
+CONSUMERS = pytest.mark.parametrize("opts", [None, {"consumer_limit": 256}], ids=["default", "capped"])
+
+
+@CONSUMERS
 @pytest.mark.parametrize("dtype", ["fp16", "bf16"])
 @pytest.mark.parametrize("length", [1, 7, 8, 4096 + 3, 1_000_003, 8 * 1024 * 1024 + 5])
-@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("offset", [0, 1, 4])
 @pytest.mark.parametrize("mode", ["sum", "copy"])
-def test_consumer_bit_exact(dtype, length, offset, mode):
+def test_consumer_bit_exact(dtype, length, offset, mode, opts):
     torch = torch_mod()
-    say(f"[consume] dtype={dtype} len={length} offset={offset} mode={mode}")
+    say(f"[consume] dtype={dtype} len={length} offset={offset} mode={mode} {opts}")
     src = workloads.uniform_bits(length + 8, 21, dtype, -4, 4)
     peer = workloads.uniform_bits(length + 8, 22, dtype, -4, 4)
     dS, dP = to_dev(src), to_dev(peer)
@@ -140,7 +146,7 @@ def test_consumer_bit_exact(dtype, length, offset, mode):
     ctr.fill_(5)
     el = 2
     fo.consume_group(dS.data_ptr() + el * offset, dP.data_ptr() + el * offset if mode == "sum" else None,
-                     dD.data_ptr() + el * offset, length, dtype, ctr, 5)
+                     dD.data_ptr() + el * offset, length, dtype, ctr, 5, opts=opts)
     torch.cuda.synchronize()
     got = from_dev(dD)[offset:offset + length]
     s, p = src[offset:offset + length], peer[offset:offset + length]
@@ -156,8 +162,9 @@ SPECIAL_BITS = {
 }
 
 
+@CONSUMERS
 @pytest.mark.parametrize("dtype", ["fp16", "bf16"])
-def test_consumer_sum_special_values(dtype):
+def test_consumer_sum_special_values(dtype, opts):
     # every pair of special values (signed zeros, subnormals, overflow of the
     # largest finite to infinity, inf - inf): the sum is the correctly
     # rounded one, bit for bit; a NaN result only has to be a NaN
@@ -167,7 +174,7 @@ def test_consumer_sum_special_values(dtype):
     src, peer = np.repeat(v, v.size), np.tile(v, v.size)       # 144 pairs: 18 vector chunks
     n = src.size
     dD = empty16(n, dtype)
-    fo.consume_group(to_dev(src), to_dev(peer), dD, n, dtype)
+    fo.consume_group(to_dev(src), to_dev(peer), dD, n, dtype, opts=opts)
     torch.cuda.synchronize()
     got = from_dev(dD)[:n]
     ref = oracle.add_rne(src, peer, dtype)
@@ -178,7 +185,8 @@ def test_consumer_sum_special_values(dtype):
     np.testing.assert_array_equal(got[~nan_ref], ref[~nan_ref])
 
 
-def test_consumer_timeout_reports_and_skips():
+@CONSUMERS
+def test_consumer_timeout_reports_and_skips(opts):
     torch = torch_mod()
     say("[consume timeout] counter never reaches the target; 2 ms limit")
     old = fo.get_poll_timeout_us()
@@ -190,7 +198,7 @@ def test_consumer_timeout_reports_and_skips():
         dD = empty16(n, "fp16")
         ctr = zeros_u32(1)
         status = zeros_u32(1)
-        fo.consume_group(dS, None, dD, n, "fp16", ctr, 1, status)
+        fo.consume_group(dS, None, dD, n, "fp16", ctr, 1, status, opts=opts)
         torch.cuda.synchronize()
         assert int(status.cpu()[0]) & 1
         assert np.all(from_dev(dD)[:n] == 0x7E00)

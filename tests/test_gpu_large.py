@@ -2,10 +2,12 @@
 
 The GEMM epilogue writes a signalled tile with 16-byte buffer stores when the
 whole output fits a 31-bit byte range, and with 8-byte device-coherent
-stores addressed in 64 bits otherwise; the consumer reads a segment with
-16-byte buffer loads when it fits 31 bits, and with 8-byte coherent loads
-otherwise. These tests run the second kind of each: a 32768 x 32768 output
-(2 GiB) and a segment of 2^30 + 37 elements. GEMM values are checked on
+stores addressed in 64 bits otherwise (the tiled kernels and the 128x128 and
+64x64 block kernels); a capped consumer reads a segment with 16-byte buffer
+loads when it fits 31 bits, and with 8-byte coherent loads otherwise, an
+uncapped one through its LDS ring whatever the size. These tests run the
+second kind of each: a 32768 x 32768 output (2 GiB) and a segment of
+2^30 + 37 elements. GEMM values are checked on
 seeded rows on both sides of the 2 GiB boundary against the exact product
 (and every element for having been written);
 the consumer input repeats one seeded block, so the whole output is
@@ -30,16 +32,18 @@ def gpu():
     fo.lib()
 
 
-def test_signalled_gemm_output_past_2_gib():
+# (64x64 tiles: 128x128 blocks, and 64x64 ones where the plan's waves are wide)
+@pytest.mark.parametrize("tile,cus,sizes", [(256, 256, [32, 32]), (64, 256, [500, 524]), (64, 1 << 17, [1, 1])])
+def test_signalled_gemm_output_past_2_gib(tile, cus, sizes):
     torch = torch_mod()
     M = N = 32768
     K = 64
-    say(f"[large GEMM] {M}x{N}x{K} row-major, signalled (8-byte coherent stores)")
+    say(f"[large GEMM] {M}x{N}x{K} tile {tile} W={cus} row-major, signalled (8-byte coherent stores)")
     assert M * N * 2 > 2**31 - 1
     A = workloads.uniform_bits((M, K), 41)
     W = workloads.uniform_bits((N, K), 42, lo=-0.125, hi=0.125)
-    plan = fo.plan_groups(M, N, K, dtype="fp16", tile_m=256, tile_n=256, order="xcd", num_cus=256,
-                          pattern="rowmajor", sizes=[32, 32])
+    plan = fo.plan_groups(M, N, K, dtype="fp16", tile_m=tile, tile_n=tile, order="xcd", num_cus=cus,
+                          pattern="rowmajor", sizes=sizes)
     dp = dev_plan(plan)
     C = torch.empty(M * N, dtype=torch.int16, device="cuda")
     C.fill_(0x7E00)                              # NaN: rows left unwritten would show
@@ -57,12 +61,14 @@ def test_signalled_gemm_output_past_2_gib():
     assert_close_bits(got, ref.reshape(-1), "fp16", "GEMM rows past 2 GiB")
 
 
+@pytest.mark.parametrize("path", ["ring", "8-byte coherent loads"])
 @pytest.mark.parametrize("mode", ["sum", "copy"])
-def test_consumer_segment_past_2_gib(mode):
+def test_consumer_segment_past_2_gib(mode, path):
     torch = torch_mod()
     block = 1 << 16
     n = (1 << 30) + 37
-    say(f"[large consume] {n} elements, {mode} (8-byte coherent loads)")
+    opts = None if path == "ring" else {"consumer_limit": 256}
+    say(f"[large consume] {n} elements, {mode} ({path})")
     sb = workloads.uniform_bits(block, 44, "bf16", -4, 4)
     pb = workloads.uniform_bits(block, 45, "bf16", -4, 4)
     reps = -(-n // block)
@@ -72,7 +78,7 @@ def test_consumer_segment_past_2_gib(mode):
     dst.fill_(0x7FC0)
     ctr = zeros_u32(1)
     ctr.fill_(1)
-    fo.consume_group(src, peer, dst, n, "bf16", ctr, 1)
+    fo.consume_group(src, peer, dst, n, "bf16", ctr, 1, opts=opts)
     torch.cuda.synchronize()
     eb = oracle.add_rne(sb, pb, "bf16") if mode == "sum" else sb
     expect = to_dev(eb).repeat(reps)[:n]
