@@ -406,7 +406,7 @@ fo_status fo_reset_counters(uint32_t* counters, int32_t n, void* stream);
  * values in dst and out, the counters as below). Its gate waits for the whole
  * GEMM besides the work queued ahead of it, so that a run whose poll_timeout_us
  * is below 10 ms or below a hundred times the GEMM's estimate has a launch per
- * group.
+ * group. Consumed together:
  *   gemm_stream: GEMM -> reset kernel (counters at their targets) -> done wait
  *   comm_stream: gate kernel -> consumer + post-reorder
  *                [-> mark kernel, when its workgroups are too many to be counted]
@@ -431,11 +431,11 @@ fo_status fo_reset_counters(uint32_t* counters, int32_t n, void* stream);
  * caller clears it, so a timeout of one run stays visible after later runs
  * queued behind it. A gate that gives up because a later run's tag has
  * already arrived leaves the word as it is (that run is not delayed). When the
- * done wait gives up it takes the run's tag out of the gate word. Groups
- * consumed together are not consumed at all once either wait has given up: the
- * launch's workgroups that find another value than the run's tag in the gate
- * word write neither dst nor out, so later work of gemm_stream (which goes on
- * after the done wait) can use both.
+ * done wait gives up it takes the run's tag out of the gate word. Where groups
+ * are consumed together, a workgroup of their launch that finds another value
+ * than the run's tag there writes neither dst nor out: what starts after a wait
+ * has given up leaves both to gemm_stream's later work (a workgroup that was
+ * running when the done wait gave up finishes its rows).
  * A group's consumer is one wait kernel on the group's counter and one
  * streaming kernel that does what fo_consume_group does for each of the
  * group's plan segments (fo_plan_segments: 1, R or B of them). Every group

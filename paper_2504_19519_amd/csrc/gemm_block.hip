@@ -17,9 +17,10 @@
 // Measured against one 64x64 form for all (four waves of 32x32, three stages,
 // one workgroup per compute unit, bf16): 768x3840x4160 51.9 -> 29.0 us (473 ->
 // 846 TFLOP/s), signalled 1216x2880x1984 47.6 -> 22.6 us, 64x4096x3584 17.0 ->
-// 9.8 us (in a run of 14.9 us; 13.3 without the loop, see Mode). What bounds it now: in the 128x128 form the LDS (32 KB in, 64 KB read
-// per 512 cycles of MFMA) and the ~5 us of a launch's prologue and epilogue; in
-// the small blocks the latency of a step's barrier and fragment reads.
+// 9.8 us (in a run of 14.9 us; 13.3 without the loop, see Mode). What bounds it
+// now: in the 128x128 form the LDS (32 KB in, 64 KB read per 512 cycles of MFMA)
+// and the ~5 us of a launch's prologue and epilogue; in the small blocks the
+// latency of a step's barrier and fragment reads.
 //
 // Main loop as in gemm.hip: direct global-to-LDS loads into a ring of ST
 // stages, XOR-swizzled rows, the next MFMA substep's fragments read during the
@@ -510,7 +511,8 @@ void launch_128(const GemmArgs& a, int grid, bool pair, hipStream_t s) {
 // land), two on a unit, 2 stages; 64x64, 4 of 64, two on a unit (64x4096x3584
 // 14.2; 3 stages 16.6; 3 of 128 14.8 but one block per unit); the small blocks,
 // steps of 128, since their MFMAs are too few to cover a barrier per 64 (64x32
-// 128x4096x3584 12.6, in steps of 64 15.7; 32x32 64x4096x3584 9.8, 11.2).
+// 128x4096x3584 12.6, in steps of 64 15.7; 32x32 64x4096x3584 9.8, 11.2). Those are
+// only taken where all of a launch's blocks run at a time (`one` holds).
 template <int DT>
 void launch_64(const GemmArgs& a, int bm, int bn, int grid, bool pair, bool one, hipStream_t s) {
     const dim3 g(grid), b(256);

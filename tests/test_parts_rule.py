@@ -36,10 +36,11 @@ def parts(tmp_path_factory):
 
 
 # tile_n, tiles, K, us in tiles, us in blocks
-RESERVED = [(128, 120, 256, 9.4, 8.0), (128, 120, 4096, 53, 34), (128, 128, 256, 9.5, 11.7), (128, 240, 1024, 20.4, 22.2),
-            (128, 240, 4096, 62, 65), (128, 300, 1024, 33.8, 29.6), (128, 300, 4096, 106, 89), (128, 360, 4096, 109, 96),
-            (128, 480, 1024, 38.3, 41), (256, 60, 1024, 25, 12.6), (256, 60, 4096, 72, 34), (256, 120, 256, 13.5, 12.4),
-            (256, 120, 4096, 75, 65), (256, 250, 4096, 161, 145), (256, 300, 4096, 163, 156), (256, 320, 1024, 51.2, 54.2)]
+RESERVED = [(128, 120, 256, 9.4, 8.0), (128, 120, 4096, 53, 34), (128, 128, 256, 9.5, 11.7),
+            (128, 240, 1024, 20.4, 22.2), (128, 240, 4096, 62, 65), (128, 300, 1024, 33.8, 29.6),
+            (128, 300, 4096, 106, 89), (128, 360, 4096, 109, 96), (128, 480, 1024, 38.3, 41),
+            (256, 60, 1024, 25, 12.6), (256, 60, 4096, 72, 34), (256, 120, 256, 13.5, 12.4), (256, 120, 4096, 75, 65),
+            (256, 250, 4096, 161, 145), (256, 300, 4096, 163, 156), (256, 320, 1024, 51.2, 54.2)]
 SHARED = [(128, 128, 4096, 52, 32), (128, 192, 4096, 55, 48), (128, 256, 1024, 20, 18), (128, 320, 4096, 107, 85),
           (128, 512, 1024, 37, 34), (256, 64, 4096, 72, 33), (256, 128, 4096, 74, 57), (256, 192, 4096, 82, 90),
           (256, 256, 4096, 101, 119), (256, 320, 4096, 168, 158), (256, 384, 1024, 55, 51), (256, 448, 4096, 190, 214)]
